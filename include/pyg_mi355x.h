@@ -641,6 +641,48 @@ int pyg_gat_scores_backward(const float *a_src, const float *a_dst, int64_t H, f
                             const pyg_csr *csr, const pyg_csr *csr_t, const int32_t *map_t, const float *grad_scores,
                             float *grad_a_src, float *grad_a_dst, void *ws, size_t ws_bytes, void *stream);
 
+/* Workspace bytes needed by pyg_gat_forward (pass csr->chunk as chunk). */
+int pyg_gat_forward_workspace(int64_t N, int64_t H, int64_t C, int64_t E, int64_t chunk, size_t *bytes);
+
+/* GAT's attention aggregation in one gather pass (the coefficients of
+ * pyg_gat_softmax and the sum of pyg_propagate_heads, never stored per edge):
+ *   out[i, h*C + c] = sum over edges j -> i of alpha[h] * x[j, h*C + c],
+ *   alpha = softmax over i's incoming edges of LeakyReLU(v), v = a_src[j,h] + a_dst[i,h].
+ * Sizes from csr->N and csr->E. x, out [N, H*C] in dtype, 16-byte aligned;
+ * a_src, a_dst fp32 [N, H]. For a later pyg_gat_backward pass all three of
+ *   all   fp32 [N, H*C]  the sums before their rounding to dtype,
+ *   plus  fp32 [N, H*C]  the part of them over edges with v >= 0,
+ *   stat  fp32 [N, H, 4] (a_dst, maximum score, 1 / sum of exponentials, sum of alpha over v >= 0),
+ * 16-byte aligned outputs, else NULL for all three. Rows without incoming
+ * edges are zero. Online softmax (running maximum, rescaled fp32 sums);
+ * deterministic. Errors: PYG_ERR_INVALID_ARG (bad dtype, H <= 0, C < 0, NULL
+ * or inconsistent csr, NULL arrays, only some of all / plus / stat, a
+ * non-finite slope), PYG_ERR_UNSUPPORTED (E = 0, C not a power-of-two count,
+ * at most 64, of 16-byte vectors, unaligned arrays, sizes >= 2^31),
+ * PYG_ERR_WORKSPACE. */
+int pyg_gat_forward(const void *x, int dtype, int64_t H, int64_t C, const float *a_src, const float *a_dst,
+                    float negative_slope, const pyg_csr *csr, void *out, float *all, float *plus, float *stat, void *ws,
+                    size_t ws_bytes, void *stream);
+
+/* Workspace bytes needed by pyg_gat_backward (pass csr_t->chunk). */
+int pyg_gat_backward_workspace(int64_t N, int64_t H, int64_t C, int64_t E, int64_t chunk_t, size_t *bytes);
+
+/* Gradients of pyg_gat_forward for g = dL/d out [N, H*C], from what that call
+ * kept, in one pass over the reversed graph (csr_t: the CSR of the reversed
+ * edge list; neither perm nor a transpose map is read):
+ *   grad_x     [N, H*C] in dtype,
+ *   grad_a_src fp32 [N, H], grad_a_dst fp32 [N, H].
+ * The values of pyg_propagate_heads_backward, pyg_segment_softmax_backward
+ * and pyg_gat_scores_backward in turn, with the target's sum of
+ * alpha * <g, x> taken as <g, all> and the score gradients of a target summed
+ * as (1 - slope) * (<g, plus> - <g, all> * sum of alpha over v >= 0).
+ * grad_out, x, grad_x in dtype and 16-byte aligned. Deterministic. Errors as
+ * pyg_gat_forward. */
+int pyg_gat_backward(const void *grad_out, const void *x, int dtype, int64_t H, int64_t C, const float *a_src,
+                     float negative_slope, const float *all, const float *plus, const float *stat,
+                     const pyg_csr *csr_t, void *grad_x, float *grad_a_src, float *grad_a_dst, void *ws,
+                     size_t ws_bytes, void *stream);
+
 /* ---- Dense feature transform of a GCN layer (Section 2 lists GCN; its
  * layer multiplies the features by a weight matrix around the normalised
  * aggregation, A (X Theta) = (A X) Theta). */

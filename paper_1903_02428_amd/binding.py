@@ -34,6 +34,7 @@ EXPORTED = [
     "pyg_propagate_noalloc", "pyg_gcn_propagate_workspace", "pyg_gcn_propagate", "pyg_csr_blocks_workspace", "pyg_csr_blocks_build", "pyg_propagate_blocked_workspace",
     "pyg_propagate_blocked", "pyg_gcn_propagate_blocked_workspace", "pyg_gcn_propagate_blocked",
     "pyg_coo_to_csr_blocked_workspace", "pyg_coo_to_csr_blocked", "pyg_degree_csr_blocks",
+    "pyg_gat_forward_workspace", "pyg_gat_forward", "pyg_gat_backward_workspace", "pyg_gat_backward",
 ]
 
 
@@ -131,6 +132,12 @@ def library() -> ctypes.CDLL:
             "pyg_gat_scores_backward_workspace": [i64, i64, i64, i64, sz],
             "pyg_gat_scores_backward": [p, p, i64, ctypes.c_float, ctypes.POINTER(_Csr), ctypes.POINTER(_Csr), p, p, p,
                                         p, p, ctypes.c_size_t, p],
+            "pyg_gat_forward_workspace": [i64, i64, i64, i64, i64, sz],
+            "pyg_gat_forward": [p, i32, i64, i64, p, p, ctypes.c_float, ctypes.POINTER(_Csr), p, p, p, p, p,
+                                ctypes.c_size_t, p],
+            "pyg_gat_backward_workspace": [i64, i64, i64, i64, i64, sz],
+            "pyg_gat_backward": [p, p, i32, i64, i64, p, ctypes.c_float, p, p, p, ctypes.POINTER(_Csr), p, p, p, p,
+                                 ctypes.c_size_t, p],
             "pyg_dense_transform": [p, i32, i64, i64, p, i64, p, i32, p, ctypes.c_size_t, p],
             "pyg_global_pool_workspace": [i32, i64, i64, i64, i32, sz],
             "pyg_global_pool": [p, i32, i64, i64, p, i64, i32, p, p, p, ctypes.c_size_t, p],
@@ -1115,12 +1122,67 @@ class Propagate(torch.autograd.Function):
         return gx, gw, None, None, None
 
 
+def _aligned16(*tensors) -> bool:
+    return all(t.data_ptr() % 16 == 0 for t in tensors)
+
+
+def _gat_fused(x: torch.Tensor, heads: int, E: int) -> bool:
+    """Whether the one-pass attention kernels take this shape: heads of a
+    power-of-two count (at most 64) of 16-byte vectors, aligned rows."""
+    lanes, odd = divmod(x.shape[1] // heads * x.element_size(), 16)
+    return E > 0 and odd == 0 and 0 < lanes <= 64 and lanes & (lanes - 1) == 0 and _aligned16(x)
+
+
+def _gat_forward(x, a_src, a_dst, csr: CSR, slope: float, need_grad: bool):
+    """(out, all, plus, stat) of pyg_gat_forward; the last three None without need_grad."""
+    lib = library()
+    _need_cuda("x", x, None, 2)
+    _need_cuda("a_src", a_src, torch.float32, 2)
+    _need_cuda("a_dst", a_dst, torch.float32, 2)
+    (N, F), H, dev = x.shape, a_src.shape[1], x.device
+    if a_src.shape != a_dst.shape or a_src.shape[0] != csr.N:
+        raise ValueError("a_src and a_dst must both be [N, H]")
+    if csr.N != N:
+        raise ValueError("csr does not match x")
+    out = torch.empty_like(x)
+    al = pl = st = None
+    if need_grad:
+        al, pl = torch.empty((2, N, F), dtype=torch.float32, device=dev).unbind(0)
+        st = torch.empty((N, H, 4), dtype=torch.float32, device=dev)
+    nbytes = _size(lib.pyg_gat_forward_workspace, N, H, F // H, csr.E, csr.chunk)
+    ws = _workspace(nbytes, dev)
+    c = csr._c()
+    _check(lib.pyg_gat_forward(_ptr(x), DTYPE[x.dtype], H, F // H, _ptr(a_src), _ptr(a_dst), ctypes.c_float(slope),
+                               ctypes.byref(c), _ptr(out), _ptr(al), _ptr(pl), _ptr(st), _ptr(ws), nbytes,
+                               _stream(dev)), "pyg_gat_forward")
+    return out, al, pl, st
+
+
+def _gat_backward(grad_out, x, a_src, kept, csr_t: CSR, slope: float):
+    """(grad_x, grad_a_src, grad_a_dst) of pyg_gat_backward."""
+    lib = library()
+    _need_cuda("grad_out", grad_out, x.dtype, 2)
+    (N, F), H, dev = x.shape, a_src.shape[1], x.device
+    if grad_out.shape != x.shape:
+        raise ValueError("grad_out must match x")
+    gx, gs, gd = torch.empty_like(x), torch.empty_like(a_src), torch.empty_like(a_src)
+    nbytes = _size(lib.pyg_gat_backward_workspace, N, H, F // H, csr_t.E, csr_t.chunk)
+    ws = _workspace(nbytes, dev)
+    c = csr_t._c()
+    _check(lib.pyg_gat_backward(_ptr(grad_out), _ptr(x), DTYPE[x.dtype], H, F // H, _ptr(a_src), ctypes.c_float(slope),
+                                _ptr(kept[0]), _ptr(kept[1]), _ptr(kept[2]), ctypes.byref(c), _ptr(gx), _ptr(gs),
+                                _ptr(gd), _ptr(ws), nbytes, _stream(dev)), "pyg_gat_backward")
+    return gx, gs, gd
+
+
 class GATAttention(torch.autograd.Function):
     """GAT's attention aggregation (Section 2): coefficients alpha =
     softmax over each target's incoming edges of LeakyReLU(a_src[j] +
     a_dst[i]) per head, then out_i = sum_j alpha_{j,i} x_j per head block.
-    Forward: gat_softmax + propagate_heads; backward: propagate_heads_backward,
-    segment_softmax_backward, gat_scores_backward (all in CSR slot order).
+    Where heads are whole 16-byte vectors: pyg_gat_forward, which stores no
+    per-edge array, and pyg_gat_backward. Otherwise gat_softmax +
+    propagate_heads, and propagate_heads_backward, segment_softmax_backward,
+    gat_scores_backward (all in CSR slot order).
     Use as GATAttention.apply(x [N, H*C], a_src [N, H], a_dst [N, H], graph,
     negative_slope); fp32 or bf16 x, fp32 logits."""
 
@@ -1128,17 +1190,27 @@ class GATAttention(torch.autograd.Function):
     def forward(ctx, x, a_src, a_dst, graph: Graph, negative_slope: float = 0.2):
         H = a_src.shape[1]
         csr = graph.plain
-        alpha = gat_softmax(a_src.detach().contiguous(), a_dst.detach().contiguous(), csr, negative_slope, "csr")
-        out = propagate_heads(x.detach().contiguous(), csr, alpha, H)
         ctx.graph, ctx.slope = graph, negative_slope
+        xc, sc, dc = x.detach().contiguous(), a_src.detach().contiguous(), a_dst.detach().contiguous()
+        if x.dim() == 2 and x.dtype in DTYPE and H > 0 and x.shape[1] % H == 0 and _gat_fused(xc, H, csr.E):
+            out, al, pl, st = _gat_forward(xc, sc, dc, csr, negative_slope, any(ctx.needs_input_grad[:3]))
+            ctx.save_for_backward(x, a_src, a_dst, None, al, pl, st)
+            return out
+        alpha = gat_softmax(sc, dc, csr, negative_slope, "csr")
+        out = propagate_heads(xc, csr, alpha, H)
         ctx.save_for_backward(x, a_src, a_dst, alpha)
         return out
 
     @staticmethod
     def backward(ctx, grad_out):
-        x, a_src, a_dst, alpha = ctx.saved_tensors
+        x, a_src, a_dst, alpha, *kept = ctx.saved_tensors
         g = ctx.graph
         H = a_src.shape[1]
+        if kept:
+            gout, xc = grad_out.contiguous().to(x.dtype), x.detach().contiguous()
+            gout, xc = (t if _aligned16(t) else t.clone() for t in (gout, xc))
+            grads = _gat_backward(gout, xc, a_src.detach().contiguous(), kept, g.csr_t, ctx.slope)
+            return tuple(v if need else None for v, need in zip(grads, ctx.needs_input_grad)) + (None, None)
         need_logits = ctx.needs_input_grad[1] or ctx.needs_input_grad[2]
         gx, galpha = propagate_heads_backward(grad_out.contiguous().to(x.dtype), x.detach().contiguous(), g.plain,
                                               g.csr_t, alpha, H, need_grad_x=ctx.needs_input_grad[0],

@@ -215,6 +215,18 @@ constexpr int kSegMsgEdgeReluGrad = 100;
 // formed in fp64 and rounded once (w = csr weight, or 1), optionally written out.
 constexpr int kSegMsgGcn = 101;
 int64_t segment_chunk(int64_t E, int64_t n_rows, int64_t requested);
+
+// The cache-policy hint for hub source rows: from rows of 512 bytes and source
+// arrays of 64 MB on (39 MB PubMed-shaped rows, F = 500, lose 20 % with it,
+// the large graph's 119 MB gain 10 %; 256-byte rows lose at every budget).
+constexpr int kHotClasses = 256;
+static inline bool hint_pays(int64_t n_rows, int64_t row_bytes) {
+    return row_bytes >= 512 && n_rows * row_bytes > (int64_t(64) << 20);
+}
+// Degree class of every row (node_class) and the class below which a row is
+// gathered non-temporally (*hot; 0 = none); class_hist: kHotClasses of scratch.
+int hot_rows(const int64_t *rowptr, int64_t n_rows, int64_t row_bytes, int32_t *class_hist, uint8_t *node_class,
+             int32_t *hot, hipStream_t s);
 // Source-blocked form: a.rowptr has B * n_rows + 1 entries (virtual row
 // b * n_rows + i = the slots of target i whose source lies in block b), a.col,
 // a.weight and a.perm are in that slot order; 2 <= B <= 32, 16-byte rows.

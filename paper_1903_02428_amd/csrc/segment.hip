@@ -34,7 +34,7 @@
 // slot, 8 lanes per sub-group), all windows in one launch, window-major, and
 // long rows are folded once after it; the hint is then off. Each window's reduction order
 // is fixed, so results stay bit-reproducible.
-#include "common.hpp"
+#include "lanes.hpp"
 
 #include <type_traits>
 
@@ -105,13 +105,6 @@ struct SegParams {
 #define PYG_LIGHT_MAX_DEGREE 16  // kNN rows of 16 slots gain 25 % as light rows
 #endif
 constexpr int64_t kLightMaxDegree = PYG_LIGHT_MAX_DEGREE;  // mean row length up to which rows go to sub-groups
-// Source arrays from 64 MB: the 39 MB PubMed-shaped rows (F = 500) lose 20 %
-// with the hint, the 119 MB large-graph rows gain 10 %.
-#ifndef PYG_HINT_MIN_MB
-#define PYG_HINT_MIN_MB 64
-#endif
-constexpr int64_t kHintMinBytes = (int64_t)PYG_HINT_MIN_MB << 20;
-constexpr int64_t kHintMinRowBytes = 512;
 constexpr int64_t kHotBudgetBytes = 12ll << 20;  // hot rows kept cacheable
 // Narrow windows: when the source rows are large in total and wider than one
 // cache line, the row is reduced one 128-byte window (32 fp32 / 64 bf16
@@ -147,81 +140,6 @@ constexpr int64_t kHotBudgetBytes = 12ll << 20;  // hot rows kept cacheable
 constexpr int64_t kWindowBytes = PYG_WINDOW_BYTES;
 constexpr int64_t kWindowMinBytes = (int64_t)PYG_WINDOW_MIN_MB << 20;
 
-// ------------------------------------------------------- lane vector types
-template <typename T, bool VEC> struct Lane;
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-template <> struct Lane<float, true> {  // 4 x fp32 = 16 B
-    using R = float4;
-    static constexpr int N = 4;
-    __device__ static R load(const float *p) { return *reinterpret_cast<const R *>(p); }
-    __device__ static R load_nt(const float *p) {
-        const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p));
-        return make_float4(v.x, v.y, v.z, v.w);
-    }
-    __device__ static R zero() { return make_float4(0.f, 0.f, 0.f, 0.f); }
-    __device__ static float get(const R &r, int e) { return e == 0 ? r.x : e == 1 ? r.y : e == 2 ? r.z : r.w; }
-    __device__ static void store(float *p, const float (&v)[N]) { *reinterpret_cast<R *>(p) = make_float4(v[0], v[1], v[2], v[3]); }
-};
-template <> struct Lane<uint16_t, true> {  // 8 x bf16 = 16 B
-    using R = uint4;
-    static constexpr int N = 8;
-    __device__ static R load(const uint16_t *p) { return *reinterpret_cast<const R *>(p); }
-    __device__ static R load_nt(const uint16_t *p) {
-        const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
-        return make_uint4(v.x, v.y, v.z, v.w);
-    }
-    __device__ static R zero() { return make_uint4(0, 0, 0, 0); }
-    __device__ static float get(const R &r, int e) {
-        const uint32_t w = (e >> 1) == 0 ? r.x : (e >> 1) == 1 ? r.y : (e >> 1) == 2 ? r.z : r.w;
-        return (e & 1) ? __uint_as_float(w & 0xFFFF0000u) : __uint_as_float(w << 16);
-    }
-    __device__ static void store(uint16_t *p, const float (&v)[N]) {
-        uint32_t o[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] = uint32_t(f32_to_bf16_rne(v[2 * i])) | (uint32_t(f32_to_bf16_rne(v[2 * i + 1])) << 16);
-        *reinterpret_cast<R *>(p) = make_uint4(o[0], o[1], o[2], o[3]);
-    }
-};
-template <> struct Lane<float, false> {
-    using R = float;
-    static constexpr int N = 1;
-    __device__ static R load(const float *p) { return *p; }
-    __device__ static R load_nt(const float *p) { return __builtin_nontemporal_load(p); }
-    __device__ static R zero() { return 0.f; }
-    __device__ static float get(const R &r, int) { return r; }
-    __device__ static void store(float *p, const float (&v)[N]) { *p = v[0]; }
-};
-template <> struct Lane<uint16_t, false> {
-    using R = uint16_t;
-    static constexpr int N = 1;
-    __device__ static R load(const uint16_t *p) { return *p; }
-    __device__ static R load_nt(const uint16_t *p) { return __builtin_nontemporal_load(p); }
-    __device__ static R zero() { return 0; }
-    __device__ static float get(const R &r, int) { return bf16_bits_to_f32(r); }
-    __device__ static void store(uint16_t *p, const float (&v)[N]) { *p = f32_to_bf16_rne(v[0]); }
-};
-
-// Stores one lane's EP results of a row: in the row dtype T, or as fp32
-// (OF32: partial rows of source blocks, folded later).
-template <typename T, bool VEC, bool OF32>
-__device__ __forceinline__ void store_out(void *out, int64_t idx, const float (&v)[Lane<T, VEC>::N]) {
-    constexpr int EP = Lane<T, VEC>::N;
-    if constexpr (OF32) {
-        float *o = static_cast<float *>(out) + idx;
-        if constexpr (VEC) {
-#pragma unroll
-            for (int k = 0; k < EP / 4; ++k)
-                reinterpret_cast<float4 *>(o)[k] = make_float4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
-        } else {
-            o[0] = v[0];
-        }
-    } else {
-        Lane<T, VEC>::store(static_cast<T *>(out) + idx, v);
-    }
-}
-
 // Degree class: 8 classes per octave, monotone in d, 0 for d <= 0.
 __device__ __forceinline__ int deg_class(int64_t d) {
     if (d <= 0) return 0;
@@ -230,7 +148,7 @@ __device__ __forceinline__ int deg_class(int64_t d) {
     const int c = oct * 8 + sub + 1;
     return c < 255 ? c : 255;
 }
-constexpr int kClasses = 256;
+constexpr int kClasses = kHotClasses;
 
 constexpr int kFull = 0, kPartial = 1;
 constexpr int kMsgSrc = 0, kMsgWeighted = 1, kMsgDiff = 2, kMsgHeads = 3;
@@ -996,14 +914,9 @@ int run_typed(const SegmentArgs &a, SegParams p, hipStream_t s) {
     // cache hint: only when the source rows do not fit in L2 (row in-degree as the hotness proxy)
     p.hot_class = nullptr;
     const int64_t hint_bytes = narrow && PYG_HINT_NARROW == 1 ? kWindowBytes : row_bytes;
-    if (!ident && a.hint && row_bytes >= kHintMinRowBytes && a.n_rows * row_bytes > kHintMinBytes &&
+    if (!ident && a.hint && hint_pays(a.n_rows, row_bytes) &&
         !(narrow && PYG_HINT_NARROW == 0)) {
-        PYG_TRY(fill<int32_t>(p.class_hist, kClasses, 0, s));
-        k_degree_classes<<<grid_for(a.n_rows, kBlock * 16, 256), kBlock, 0, s>>>(a.rowptr, a.n_rows, p.node_class,
-                                                                                   p.class_hist);
-        PYG_LAUNCH_CHECK();
-        k_pick_hot_class<<<1, kWave, 0, s>>>(p.class_hist, kHotBudgetBytes / hint_bytes, p.hot_slot);
-        PYG_LAUNCH_CHECK();
+        PYG_TRY(hot_rows(a.rowptr, a.n_rows, hint_bytes, p.class_hist, p.node_class, p.hot_slot, s));
         p.hot_class = p.hot_slot;
     }
     // lane vectors covered by one launch (NS = 4, or one narrow window)
@@ -1261,6 +1174,16 @@ BlockedWs carve_blocked(void *base, int64_t E, int64_t N, int64_t F, int64_t B, 
 }
 
 }  // namespace
+
+int hot_rows(const int64_t *rowptr, int64_t n_rows, int64_t row_bytes, int32_t *class_hist, uint8_t *node_class,
+             int32_t *hot, hipStream_t s) {
+    PYG_TRY(fill<int32_t>(class_hist, kClasses, 0, s));
+    k_degree_classes<<<grid_for(n_rows, kBlock * 16, 256), kBlock, 0, s>>>(rowptr, n_rows, node_class, class_hist);
+    PYG_LAUNCH_CHECK();
+    k_pick_hot_class<<<1, kWave, 0, s>>>(class_hist, kHotBudgetBytes / row_bytes, hot);
+    PYG_LAUNCH_CHECK();
+    return PYG_OK;
+}
 
 size_t segment_blocked_workspace(int64_t E, int64_t N, int64_t F, int64_t B, int aggr, int64_t chunk) {
     return carve_blocked(nullptr, E, N, F, B, aggr, segment_chunk(E, B * N, chunk)).bytes;
