@@ -138,25 +138,26 @@ struct GatForward {
         }
         const float k = pexp(m, mx);
         m = mx;
-        z *= k, zp *= k;
+        // the batch is summed by itself first: shorter rounding chains
+        float bz = 0.f, bzp = 0.f, ba[EP], bp[EP];
 #pragma unroll
-        for (int e = 0; e < EP; ++e) {
-            all[e] *= k;
-            if constexpr (GRAD) plus[e] *= k;
-        }
+        for (int e = 0; e < EP; ++e) ba[e] = bp[e] = 0.f;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (!ok[u]) continue;
-            const float w = pexp(sc[u], mx);
-            z += w;
-            const float wp = pos[u] ? w : 0.f;
-            zp += wp;
+        for (int u = 0; u < U; ++u) {  // no slot: score -inf, weight 0, row 0
+            const float w = pexp(sc[u], mx), wp = pos[u] ? w : 0.f;
+            bz += w, bzp += wp;
 #pragma unroll
             for (int e = 0; e < EP; ++e) {
                 const float xv = LN::get(v[u], e);
-                all[e] = fmaf(w, xv, all[e]);
-                if constexpr (GRAD) plus[e] = fmaf(wp, xv, plus[e]);
+                ba[e] = fmaf(w, xv, ba[e]);
+                if constexpr (GRAD) bp[e] = fmaf(wp, xv, bp[e]);
             }
+        }
+        z = fmaf(z, k, bz), zp = fmaf(zp, k, bzp);
+#pragma unroll
+        for (int e = 0; e < EP; ++e) {
+            all[e] = fmaf(all[e], k, ba[e]);
+            if constexpr (GRAD) plus[e] = fmaf(plus[e], k, bp[e]);
         }
     }
     __device__ __forceinline__ void store(int64_t r) {
@@ -387,19 +388,25 @@ struct GatBackward {
             for (int e = 0; e < EP; ++e) d[u] = fmaf(LN::get(v[u], e), xo[e], d[u]);
         }
         group_sum(d, p.lgc);
+        float bg = 0.f, ba[EP];
+#pragma unroll
+        for (int e = 0; e < EP; ++e) ba[e] = 0.f;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (!ok[u]) continue;
             const float s = as + tb[u].x;
-            const float al = pexp(leaky(s, p.slope), tb[u].y) * tb[u].z;
+            const float al = ok[u] ? pexp(leaky(s, p.slope), tb[u].y) * tb[u].z : 0.f;
             const float ds = al * (d[u] - tb[u].w);
-            gs += s >= 0.f ? ds : p.slope * ds;
+            bg += s >= 0.f ? ds : p.slope * ds;
 #pragma unroll
-            for (int e = 0; e < EP; ++e) acc[e] = fmaf(al, LN::get(v[u], e), acc[e]);
+            for (int e = 0; e < EP; ++e) ba[e] = fmaf(al, LN::get(v[u], e), ba[e]);
         }
+        gs += bg;
+#pragma unroll
+        for (int e = 0; e < EP; ++e) acc[e] += ba[e];
     }
     __device__ __forceinline__ void run(int64_t r, int64_t s, int64_t t, int kind, int64_t slot) {
         begin(r);
+        float total = 0.f;
         int nx = (s + lane < t) ? column(p, s + lane, hot) : 0;
         for (int64_t base = s; base < t; base += kWave) {
             const int n = static_cast<int>(uniform64((t - base) < kWave ? (t - base) : kWave));
@@ -416,7 +423,9 @@ struct GatBackward {
                 }
                 take(jj, ok);
             }
+            total += gs, gs = 0.f;  // per batch: shorter rounding chains
         }
+        gs = total;
         for (int off = L; off < kWave; off <<= 1) {
             gs += __shfl_xor(gs, off, kWave);
 #pragma unroll
@@ -571,7 +580,7 @@ constexpr int64_t kLight = 16;
 
 template <typename T, bool GRAD>
 int launch_forward(const GatParams &p, hipStream_t s) {
-    constexpr int U = 8;
+    constexpr int U = 4;
     const int64_t items = p.zero_items + p.walk.nchunks * p.nwin;
     const unsigned grid = static_cast<unsigned>((items + 3) / 4);
     const bool light = p.lg < 6 && p.walk.E <= kLight * p.walk.N;
