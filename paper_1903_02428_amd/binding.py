@@ -1111,8 +1111,7 @@ class Propagate(torch.autograd.Function):
         g = ctx.graph
         csr, csr_t = g.plain, g.plain_t
         if edge_weight is not None:
-            w = edge_weight.detach().contiguous()
-            csr = CSR(csr.rowptr, csr.col, csr.perm, gather_edges(csr.perm, w), csr.N, csr.E, csr.chunk)
+            w = edge_weight.detach().contiguous()  # the backward reads no weights of csr itself
             csr_t = CSR(csr_t.rowptr, csr_t.col, csr_t.perm, gather_edges(csr_t.perm, w), csr_t.N, csr_t.E,
                         csr_t.chunk)
         need_w = edge_weight is not None and ctx.needs_input_grad[1]

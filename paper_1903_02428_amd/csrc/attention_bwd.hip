@@ -25,7 +25,12 @@ namespace {
 // most 16) get 64-slot chunks, so the walks are short and the wavefronts
 // many; on a 13k-edge graph the 1024-slot chunks left the head dot products
 // at 260 us.
-inline int64_t walk_chunk(int64_t E, int64_t N, int64_t dflt) { return E <= 16 * N ? 64 : dflt; }
+// Graphs with fewer than 8,192 chunks get smaller ones down to 64 slots.
+inline int64_t walk_chunk(int64_t E, int64_t N, int64_t dflt) {
+    int64_t c = E <= 16 * N ? 64 : dflt;
+    while (c > 64 && E < c * 8192) c >>= 1;
+    return c;
+}
 
 // inv[perm[p]] = p: the CSR slot of every edge id (ids outside [0, E) are
 // skipped: a malformed permutation cannot write out of bounds).

@@ -21,7 +21,7 @@
 // (edge rows reached through the transpose map or the edge ids), the edge
 // gradient is one pass over the CSR slots; max routes as above. fp32 or bf16
 // operands; bf16 gradients keep fp32 intermediates and are rounded once.
-#include "common.hpp"
+#include "lanes.hpp"
 
 #ifndef PYG_SDDMM_U
 #define PYG_SDDMM_U 4  // slots per sub-group in flight in the weight-gradient dot products
@@ -35,18 +35,12 @@ namespace {
 // most 16) get 64-slot chunks, so the walks are short and the wavefronts
 // many; on a 13k-edge graph the 1024-slot chunks left these kernels at
 // 130-260 us.
-inline int64_t walk_chunk(int64_t E, int64_t N, int64_t dflt) { return E <= 16 * N ? 64 : dflt; }
-
-template <typename T>
-__device__ __forceinline__ float ld(const T *p, int64_t i) {
-    if constexpr (sizeof(T) == 2) return bf16_bits_to_f32(reinterpret_cast<const uint16_t *>(p)[i]);
-    else return p[i];
-}
-
-template <typename T>
-__device__ __forceinline__ void st(T *p, int64_t i, float v) {
-    if constexpr (sizeof(T) == 2) reinterpret_cast<uint16_t *>(p)[i] = f32_to_bf16_rne(v);
-    else p[i] = v;
+// Graphs with fewer than 8,192 chunks get smaller ones down to 64 slots: 2M
+// edges in 1,024-slot chunks were 1,954 wavefronts, a third of the chip.
+inline int64_t walk_chunk(int64_t E, int64_t N, int64_t dflt) {
+    int64_t c = E <= 16 * N ? 64 : dflt;
+    while (c > 64 && E < c * 8192) c >>= 1;
+    return c;
 }
 
 // g'[i,:] = g[i,:] / deg_i (mean; 0 for empty rows) or g[i,:] (sum), in fp32.
@@ -220,6 +214,12 @@ __global__ void k_cast_out(const float *__restrict__ acc, int64_t n, T *__restri
         st(out, t, acc[t]);
 }
 
+// Scratch of the sum over the reversed graph, by either kernel.
+size_t reduce_workspace(int64_t E, int64_t F, int64_t chunk_t, int64_t N) {
+    const size_t a = segment_workspace(E, F, PYG_SUM, chunk_t, N), b = fused_backward_workspace(N, F, E, chunk_t);
+    return a > b ? a : b;
+}
+
 struct BwdWs {
     void *gscaled;
     float *acc;
@@ -237,7 +237,7 @@ BwdWs carve_bwd(void *base, int dtype, int64_t N, int64_t F, int64_t E, int aggr
     w.gscaled = c.take<float>(aggr != PYG_MAX && (aggr == PYG_MEAN || bf16) ? N * F : 0);
     w.acc = c.take<float>(bf16 ? N * F : 0);
     w.inv = c.take<int32_t>(aggr == PYG_MAX ? E : 0);
-    w.seg_bytes = aggr == PYG_MAX ? 0 : segment_workspace(E, F, PYG_SUM, chunk_t, N);
+    w.seg_bytes = aggr == PYG_MAX ? 0 : reduce_workspace(E, F, chunk_t, N);
     w.seg = c.take<char>(w.seg_bytes);
     w.bytes = c.used + 256;
     return w;
@@ -250,6 +250,26 @@ int backward_typed(const void *grad_out, const void *x, int dtype, int64_t N, in
     const bool w_csr = w_order == PYG_ORDER_CSR;
     const T *g = static_cast<const T *>(grad_out);
     const int64_t NF = N * F;
+    if (grad_w && !w_csr && aggr != PYG_MAX) {
+        // grad_w by edge id beside grad_x: one pass over the reversed graph.
+        // Slot order keeps the pass over csr, whose stores are coalesced.
+        FusedBackwardArgs f{};
+        f.rowptr = csr_t->rowptr, f.col = csr_t->col, f.perm = csr_t->perm, f.weight = csr_t->weight;
+        f.N = N, f.E = E, f.F = F, f.chunk = csr_t->chunk;
+        f.msg = PYG_MSG_SRC;
+        f.g = aggr == PYG_MEAN ? w.gscaled : grad_out;
+        f.g_dtype = aggr == PYG_MEAN ? PYG_F32 : dtype;
+        f.x = x, f.dtype = dtype;
+        f.grad_x = grad_x, f.grad_w = grad_w;
+        if (fused_backward_ok(f)) {
+            if (aggr == PYG_MEAN) {
+                k_scale_rows<T><<<grid_for(NF, kBlock * 4), kBlock, 0, s>>>(g, csr->rowptr, N, F, 1,
+                                                                            static_cast<float *>(w.gscaled));
+                PYG_LAUNCH_CHECK();
+            }
+            return fused_backward(f, w.seg, w.seg_bytes, s);
+        }
+    }
     if (grad_w) PYG_TRY(fill<float>(grad_w, E, 0.f, s));
     if (aggr == PYG_MAX) {
         float *acc = sizeof(T) == 4 ? static_cast<float *>(grad_x) : w.acc;
@@ -274,19 +294,20 @@ int backward_typed(const void *grad_out, const void *x, int dtype, int64_t N, in
         }
         return PYG_OK;
     }
-    // g' = s g in fp32 (only fp32 sum can read grad_out directly)
-    const bool bf16 = sizeof(T) == 2;
-    const float *gs = reinterpret_cast<const float *>(grad_out);
+    // g' = s g in fp32; a sum of source messages reads grad_out directly and
+    // rounds once itself, also in bf16
+    const bool bf16 = sizeof(T) == 2 && (aggr == PYG_MEAN || msg == PYG_MSG_DIFF);
+    const void *gs = grad_out;
     if (aggr == PYG_MEAN || bf16) {
         k_scale_rows<T><<<grid_for(NF, kBlock * 4), kBlock, 0, s>>>(g, csr ? csr->rowptr : nullptr, N, F,
                                                                     aggr == PYG_MEAN, static_cast<float *>(w.gscaled));
         PYG_LAUNCH_CHECK();
-        gs = static_cast<const float *>(w.gscaled);
+        gs = w.gscaled;
     }
     float *gx32 = bf16 ? w.acc : static_cast<float *>(grad_x);
     SegmentArgs a{};
     a.x = gs;
-    a.dtype = PYG_F32;
+    a.dtype = aggr == PYG_MEAN || bf16 ? PYG_F32 : dtype;
     a.F = F;
     a.rowptr = csr_t->rowptr;
     a.col = csr_t->col;
@@ -311,6 +332,10 @@ int backward_typed(const void *grad_out, const void *x, int dtype, int64_t N, in
         PYG_LAUNCH_CHECK();
     }
     if (grad_w && E > 0) {
+        // fp32 mean: the scaled rows themselves, as the one-pass form reads them
+        const bool scaled = sizeof(T) == 4 && aggr == PYG_MEAN;
+        if (scaled) g = static_cast<const T *>(gs);
+        const int mean = aggr == PYG_MEAN && !scaled;
         const int64_t kChunk = walk_chunk(E, N, 1024);
         const int64_t nchunks = (E + kChunk - 1) / kChunk;
         const unsigned grid = static_cast<unsigned>((nchunks + 3) / 4);
@@ -321,63 +346,17 @@ int backward_typed(const void *grad_out, const void *x, int dtype, int64_t N, in
             int lg = 0;
             while ((int64_t(1) << lg) < F / EP && lg < 6) ++lg;
             k_sddmm_vec<T, PYG_SDDMM_U><<<grid, kBlock, 0, s>>>(g, static_cast<const T *>(x), N, F, csr->rowptr, csr->col,
-                                                      w_csr ? nullptr : csr->perm, E, kChunk, lg, aggr == PYG_MEAN,
+                                                      w_csr ? nullptr : csr->perm, E, kChunk, lg, mean,
                                                       grad_w);
         } else {
             int lg = 0;
             while ((1 << lg) < F && lg < 6) ++lg;
             k_sddmm<T><<<grid, kBlock, 0, s>>>(g, static_cast<const T *>(x), N, F, csr->rowptr, csr->col,
-                                               w_csr ? nullptr : csr->perm, E, kChunk, lg, aggr == PYG_MEAN, grad_w);
+                                               w_csr ? nullptr : csr->perm, E, kChunk, lg, mean, grad_w);
         }
         PYG_LAUNCH_CHECK();
     }
     return PYG_OK;
-}
-
-// V consecutive elements of p as floats / stored from floats: V = 4 is one
-// 16-byte fp32 or 8-byte bf16 vector, V = 8 one 16-byte bf16 vector or two
-// fp32 ones (the caller checks alignment).
-template <typename T, int V>
-__device__ __forceinline__ void ldv(const T *p, float (&o)[V]) {
-    if constexpr (V == 1) {
-        o[0] = ld(p, 0);
-    } else if constexpr (sizeof(T) == 4) {
-#pragma unroll
-        for (int h = 0; h < V / 4; ++h) {
-            const float4 v = reinterpret_cast<const float4 *>(p)[h];
-            o[4 * h] = v.x, o[4 * h + 1] = v.y, o[4 * h + 2] = v.z, o[4 * h + 3] = v.w;
-        }
-    } else if constexpr (V == 4) {
-        const uint2 v = *reinterpret_cast<const uint2 *>(p);
-        o[0] = bf16_bits_to_f32(v.x & 0xFFFFu), o[1] = bf16_bits_to_f32(v.x >> 16);
-        o[2] = bf16_bits_to_f32(v.y & 0xFFFFu), o[3] = bf16_bits_to_f32(v.y >> 16);
-    } else {
-        const uint4 v = *reinterpret_cast<const uint4 *>(p);
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int h = 0; h < 4; ++h)
-            o[2 * h] = bf16_bits_to_f32(w[h] & 0xFFFFu), o[2 * h + 1] = bf16_bits_to_f32(w[h] >> 16);
-    }
-}
-
-template <typename T, int V>
-__device__ __forceinline__ void stv(T *p, const float (&o)[V]) {
-    if constexpr (V == 1) {
-        st(p, 0, o[0]);
-    } else if constexpr (sizeof(T) == 4) {
-#pragma unroll
-        for (int h = 0; h < V / 4; ++h)
-            reinterpret_cast<float4 *>(p)[h] = make_float4(o[4 * h], o[4 * h + 1], o[4 * h + 2], o[4 * h + 3]);
-    } else {
-        uint32_t w[V / 2];
-#pragma unroll
-        for (int h = 0; h < V / 2; ++h)
-            w[h] = uint32_t(f32_to_bf16_rne(o[2 * h])) | (uint32_t(f32_to_bf16_rne(o[2 * h + 1])) << 16);
-        if constexpr (V == 4)
-            *reinterpret_cast<uint2 *>(p) = make_uint2(w[0], w[1]);
-        else
-            *reinterpret_cast<uint4 *>(p) = make_uint4(w[0], w[1], w[2], w[3]);
-    }
 }
 
 // grad_e[row(p)] for every CSR slot p = (j -> i): d = gs[i] (the scaled
@@ -496,7 +475,7 @@ EdgeBwdWs carve_edge_bwd(void *base, int dtype, int64_t N, int64_t F, int64_t E,
     w.ea32 = c.take<float>(widen ? E * F : 0);
     w.inv = c.take<int32_t>(E);
     w.map = c.take<int32_t>(aggr == PYG_MAX ? 0 : E);
-    w.seg_bytes = aggr == PYG_MAX ? 0 : segment_workspace(E, F, PYG_SUM, chunk_t, N);
+    w.seg_bytes = aggr == PYG_MAX ? 0 : reduce_workspace(E, F, chunk_t, N);
     w.seg = c.take<char>(static_cast<int64_t>(w.seg_bytes));
     w.bytes = c.used + 256;
     return w;
@@ -566,6 +545,20 @@ int edge_backward_typed(const T *g, const T *xf, const T *ea, int64_t N, int64_t
     if (aggr == PYG_MEAN) {
         k_scale_rows<T><<<grid_for(NF, kBlock * 4), kBlock, 0, s>>>(g, csr->rowptr, N, F, 1, w.gs);
         PYG_LAUNCH_CHECK();
+    }
+    if (gx && ge && coo) {
+        // both gradients, by edge id: one pass over the reversed graph
+        FusedBackwardArgs f{};
+        f.rowptr = csr_t->rowptr, f.col = csr_t->col, f.perm = csr_t->perm;
+        f.N = N, f.E = E, f.F = F, f.chunk = csr_t->chunk;
+        f.msg = msg;
+        f.g = aggr == PYG_MEAN ? static_cast<const void *>(w.gs) : static_cast<const void *>(g);
+        f.g_dtype = aggr == PYG_MEAN || !bf16 ? PYG_F32 : PYG_BF16;
+        f.x = msg == PYG_MSG_EDGE_ADD ? nullptr : xf;
+        f.edge_attr = msg == PYG_MSG_EDGE_ADD ? nullptr : ea;
+        f.dtype = bf16 ? PYG_BF16 : PYG_F32;
+        f.grad_x = gx, f.grad_e = ge;
+        if (fused_backward_ok(f)) return fused_backward(f, w.seg, w.seg_bytes, s);
     }
     const bool widen = bf16 && aggr == PYG_MEAN && msg != PYG_MSG_EDGE_ADD;
     if (gx) {

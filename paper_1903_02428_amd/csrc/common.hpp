@@ -216,6 +216,11 @@ constexpr int kSegMsgEdgeReluGrad = 100;
 constexpr int kSegMsgGcn = 101;
 int64_t segment_chunk(int64_t E, int64_t n_rows, int64_t requested);
 
+// Folds the pieces of the long rows (sum): part [2 * nchunks, F] and head_row
+// [nchunks] as the segment kernel's walk writes them.
+int segment_fold_pieces(const int64_t *rowptr, int64_t n_rows, int64_t E, int64_t F, int64_t chunk, int32_t *head_row,
+                        float *part, void *out, int dtype, hipStream_t s);
+
 // The cache-policy hint for hub source rows: from rows of 512 bytes and source
 // arrays of 64 MB on (39 MB PubMed-shaped rows, F = 500, lose 20 % with it,
 // the large graph's 119 MB gain 10 %; 256-byte rows lose at every budget).
@@ -236,6 +241,28 @@ size_t segment_blocked_workspace(int64_t E, int64_t n_rows, int64_t F, int64_t B
 int segment_reduce_blocked(const SegmentArgs &a, int64_t B, void *ws, size_t ws_bytes, hipStream_t s);
 size_t segment_workspace(int64_t E, int64_t F, int aggr, int64_t chunk, int64_t n_rows);
 int segment_reduce(const SegmentArgs &a, void *ws, size_t ws_bytes, hipStream_t s);
+
+// Both gradients of a weighted (msg PYG_MSG_SRC) or edge-feature propagate in
+// one pass over the reversed CSR (sum; mean with rows g already scaled).
+struct FusedBackwardArgs {
+    const int64_t *rowptr;  // the reversed CSR
+    const int32_t *col;
+    const int64_t *perm;    // edge id of every slot
+    const float *weight;    // slot order (PYG_MSG_SRC)
+    int64_t N, E, F, chunk;
+    int msg;
+    const void *g;          // [N, F] in g_dtype (dtype, or fp32)
+    int g_dtype;
+    const void *x;          // [N, F] in dtype; not read by x_j + e
+    const void *edge_attr;  // [E, F] in dtype, edge ids; not read by x_j + e
+    int dtype;
+    void *grad_x;           // [N, F] in dtype
+    float *grad_w;          // [E], edge ids (PYG_MSG_SRC)
+    void *grad_e;           // [E, F] in dtype, edge ids (edge messages)
+};
+size_t fused_backward_workspace(int64_t N, int64_t F, int64_t E, int64_t chunk);
+bool fused_backward_ok(const FusedBackwardArgs &a);
+int fused_backward(const FusedBackwardArgs &a, void *ws, size_t ws_bytes, hipStream_t s);
 
 // inv[perm[p]] = p for a CSR's slot -> edge-id permutation (ids outside
 // [0, E) skipped); transpose_map: map_t[q] = the csr slot of the edge in

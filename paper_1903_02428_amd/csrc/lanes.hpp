@@ -83,4 +83,62 @@ __device__ __forceinline__ void store_out(void *out, int64_t idx, const float (&
     }
 }
 
+template <typename T>
+__device__ __forceinline__ float ld(const T *p, int64_t i) {
+    if constexpr (sizeof(T) == 2) return bf16_bits_to_f32(reinterpret_cast<const uint16_t *>(p)[i]);
+    else return p[i];
+}
+
+template <typename T>
+__device__ __forceinline__ void st(T *p, int64_t i, float v) {
+    if constexpr (sizeof(T) == 2) reinterpret_cast<uint16_t *>(p)[i] = f32_to_bf16_rne(v);
+    else p[i] = v;
+}
+
+// V consecutive elements of p as floats / stored from floats: V = 4 is one
+// 16-byte fp32 or 8-byte bf16 vector, V = 8 one 16-byte bf16 vector or two
+// fp32 ones (the caller checks alignment).
+template <typename T, int V>
+__device__ __forceinline__ void ldv(const T *p, float (&o)[V]) {
+    if constexpr (V == 1) {
+        o[0] = ld(p, 0);
+    } else if constexpr (sizeof(T) == 4) {
+#pragma unroll
+        for (int h = 0; h < V / 4; ++h) {
+            const float4 v = reinterpret_cast<const float4 *>(p)[h];
+            o[4 * h] = v.x, o[4 * h + 1] = v.y, o[4 * h + 2] = v.z, o[4 * h + 3] = v.w;
+        }
+    } else if constexpr (V == 4) {
+        const uint2 v = *reinterpret_cast<const uint2 *>(p);
+        o[0] = bf16_bits_to_f32(v.x & 0xFFFFu), o[1] = bf16_bits_to_f32(v.x >> 16);
+        o[2] = bf16_bits_to_f32(v.y & 0xFFFFu), o[3] = bf16_bits_to_f32(v.y >> 16);
+    } else {
+        const uint4 v = *reinterpret_cast<const uint4 *>(p);
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int h = 0; h < 4; ++h)
+            o[2 * h] = bf16_bits_to_f32(w[h] & 0xFFFFu), o[2 * h + 1] = bf16_bits_to_f32(w[h] >> 16);
+    }
+}
+
+template <typename T, int V>
+__device__ __forceinline__ void stv(T *p, const float (&o)[V]) {
+    if constexpr (V == 1) {
+        st(p, 0, o[0]);
+    } else if constexpr (sizeof(T) == 4) {
+#pragma unroll
+        for (int h = 0; h < V / 4; ++h)
+            reinterpret_cast<float4 *>(p)[h] = make_float4(o[4 * h], o[4 * h + 1], o[4 * h + 2], o[4 * h + 3]);
+    } else {
+        uint32_t w[V / 2];
+#pragma unroll
+        for (int h = 0; h < V / 2; ++h)
+            w[h] = uint32_t(f32_to_bf16_rne(o[2 * h])) | (uint32_t(f32_to_bf16_rne(o[2 * h + 1])) << 16);
+        if constexpr (V == 4)
+            *reinterpret_cast<uint2 *>(p) = make_uint2(w[0], w[1]);
+        else
+            *reinterpret_cast<uint4 *>(p) = make_uint4(w[0], w[1], w[2], w[3]);
+    }
+}
+
 }  // namespace pyg

@@ -1175,6 +1175,22 @@ BlockedWs carve_blocked(void *base, int64_t E, int64_t N, int64_t F, int64_t B, 
 
 }  // namespace
 
+int segment_fold_pieces(const int64_t *rowptr, int64_t n_rows, int64_t E, int64_t F, int64_t chunk, int32_t *head_row,
+                        float *part, void *out, int dtype, hipStream_t s) {
+    SegParams p{};
+    p.F = F;
+    p.fcnt = F;
+    p.rowptr = rowptr;
+    p.n_rows = n_rows;
+    p.E = E;
+    p.chunk = chunk;
+    p.nchunks = (E + chunk - 1) / chunk;
+    p.out = out;
+    p.part_val = part;
+    p.head_row = head_row;
+    return dtype == PYG_BF16 ? launch_fixup<uint16_t, false>(p, s) : launch_fixup<float, false>(p, s);
+}
+
 int hot_rows(const int64_t *rowptr, int64_t n_rows, int64_t row_bytes, int32_t *class_hist, uint8_t *node_class,
              int32_t *hot, hipStream_t s) {
     PYG_TRY(fill<int32_t>(class_hist, kClasses, 0, s));
