@@ -71,6 +71,30 @@ __device__ __forceinline__ uint4 load_a(const uint16_t *__restrict__ x, int64_t 
     }
 }
 
+// Four consecutive outputs of one row, from column `col` on.
+template <typename TO>
+__device__ __forceinline__ void store4(TO *__restrict__ out, int64_t row, int64_t col, int64_t Fo, const f32x4 &v,
+                                       bool vec) {
+    if (col >= Fo) return;
+    TO *o = out + row * Fo + col;
+    if (vec && col + 4 <= Fo) {
+        if constexpr (sizeof(TO) == 4) {
+            *reinterpret_cast<float4 *>(o) = make_float4(v[0], v[1], v[2], v[3]);
+        } else {
+            const uint32_t lo = uint32_t(f32_to_bf16_rne(v[0])) | (uint32_t(f32_to_bf16_rne(v[1])) << 16);
+            const uint32_t hi = uint32_t(f32_to_bf16_rne(v[2])) | (uint32_t(f32_to_bf16_rne(v[3])) << 16);
+            *reinterpret_cast<uint2 *>(o) = make_uint2(lo, hi);
+        }
+        return;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        if (col + j >= Fo) break;
+        if constexpr (sizeof(TO) == 4) o[j] = v[j];
+        else o[j] = f32_to_bf16_rne(v[j]);
+    }
+}
+
 // Store a wavefront's 32 x 128 tile: lane holds node r0 + 16t + li and
 // output features c0 + 16u + 4lg + j (j = 0..3).
 template <typename TO>
@@ -82,27 +106,7 @@ __device__ __forceinline__ void store_tile(TO *__restrict__ out, int64_t N, int6
         const int64_t row = r0 + 16 * t + li;
         if (row >= N) continue;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int64_t col = c0 + 16 * u + 4 * lg;
-            if (col >= Fo) continue;
-            TO *o = out + row * Fo + col;
-            if (vec_out && col + 4 <= Fo) {
-                if constexpr (sizeof(TO) == 4) {
-                    *reinterpret_cast<float4 *>(o) = make_float4(acc[t][u][0], acc[t][u][1], acc[t][u][2], acc[t][u][3]);
-                } else {
-                    const uint32_t lo = uint32_t(f32_to_bf16_rne(acc[t][u][0])) | (uint32_t(f32_to_bf16_rne(acc[t][u][1])) << 16);
-                    const uint32_t hi = uint32_t(f32_to_bf16_rne(acc[t][u][2])) | (uint32_t(f32_to_bf16_rne(acc[t][u][3])) << 16);
-                    *reinterpret_cast<uint2 *>(o) = make_uint2(lo, hi);
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (col + j >= Fo) break;
-                    if constexpr (sizeof(TO) == 4) o[j] = acc[t][u][j];
-                    else o[j] = f32_to_bf16_rne(acc[t][u][j]);
-                }
-            }
-        }
+        for (int u = 0; u < 8; ++u) store4(out, row, c0 + 16 * u + 4 * lg, Fo, acc[t][u], vec_out);
     }
 }
 
@@ -229,12 +233,10 @@ __global__ __launch_bounds__(kBlock) void k_dense(const uint16_t *__restrict__ x
 // lane group lg holds k = 16 s + 4 lg + e in both operands, so the four
 // steps cover the 16 k of the block with A and B paired on the same k (the
 // order of the k inside a block is a relabelling of the sum, which the
-// matrix unit adds in fp32 either way). K is staged 64 at a time.
-constexpr int kChunkF = 64;
+// matrix unit adds in fp32 either way).
 #ifndef PYG_DENSE_F32_PERSIST
-#define PYG_DENSE_F32_PERSIST 1
+#define PYG_DENSE_F32_PERSIST 2
 #endif
-constexpr int kLdsStrideF = kChunkF + 4;  // floats per LDS row; +16 B skews the banks
 
 __global__ void k_theta_t_f32(const float *__restrict__ theta, int64_t Fi, int64_t Fo, int64_t Kp, int64_t Fo_pad,
                               float *__restrict__ tt) {
@@ -261,60 +263,113 @@ __device__ __forceinline__ f32x4 load_af(const float *__restrict__ x, int64_t N,
     }
 }
 
-template <typename TO, bool VEC>
-__global__ __launch_bounds__(kBlock) void k_dense_f32(const float *__restrict__ x, int64_t N, int64_t Fi, int64_t Kp,
-                                                      const float *__restrict__ tt, int64_t Fo, TO *__restrict__ out) {
-    __shared__ __align__(16) float lds[kCols * kLdsStrideF];
+// A workgroup owns 16 * 4 / WC rows and 16 * NU * WC columns: WC wavefronts
+// side by side, each 16 rows by NU tiles of 16 columns, so that no tile of a
+// narrow Theta is padding and a graph of 20k nodes still gives every SIMD a
+// few wavefronts (rows of 32 and 128-column tiles gave it 0.6, and half of
+// the tiles were padding for 64 columns). Theta is staged as it lies, KC rows
+// of it at a time, double-buffered in LDS (row stride 4 mod 16 floats: the 64
+// lanes of an operand read fall into different banks), the next stage's X and
+// Theta loaded before this one is multiplied. 19,717 x 500 -> 64: 57 + 5 us
+// (the transposing launch) before, 25 us now; the matrix cores alone need 8 us
+// at the fp32 rate, X and the output 9 us.
+template <typename TO, bool VEC, int NU, int WC, int KC>
+__global__ __launch_bounds__(kBlock) void k_dense_f32(const float *__restrict__ x, int64_t N, int64_t Fi,
+                                                      const float *__restrict__ theta, int64_t Fo, bool tvec,
+                                                      TO *__restrict__ out) {
+    constexpr int WR = kBlock / kWave / WC, COLS = 16 * NU * WC, CS = COLS + 4;
+    constexpr int SA = KC / 16;                    // 16-k steps of a stage
+    constexpr int SB = KC * COLS / 4 / kBlock;     // 16-byte pieces of Theta per thread and stage
+    static_assert(SB * kBlock * 4 == KC * COLS, "whole pieces per thread");
+    __shared__ __align__(16) float lds[2][KC * CS];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
-    const int64_t r0 = (int64_t)blockIdx.x * (kRowsWave * (kBlock / kWave)) + wave * kRowsWave;
-    const int64_t c0 = (int64_t)blockIdx.y * kCols;
+    const int64_t row = ((int64_t)blockIdx.x * WR + wave / WC) * 16 + (lane & 15);
+    const int64_t c0 = (int64_t)blockIdx.y * COLS;
+    const int cw = (wave % WC) * (16 * NU);
     const int li = lane & 15, lg = lane >> 4;
 
-    f32x4 acc[2][8];
+    auto load_x = [&](int64_t kc, f32x4 (&a)[SA]) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+        for (int st = 0; st < SA; ++st) a[st] = load_af<VEC>(x, N, Fi, row, kc + 16 * st + 4 * lg);
+    };
+    auto load_theta = [&](int64_t kc, f32x4 (&b)[SB]) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc[t][u] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    for (int64_t kc = 0; kc < Kp; kc += kChunkF) {
-        const int kn = static_cast<int>((Kp - kc) < kChunkF ? (Kp - kc) : kChunkF);  // multiple of 16
-        f32x4 a[2][kChunkF / 16];
-#pragma unroll
-        for (int st = 0; st < kChunkF / 16; ++st)
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-                a[t][st] = (st * 16 < kn) ? load_af<VEC>(x, N, Fi, r0 + 16 * t + li, kc + 16 * st + 4 * lg)
-                                          : f32x4{0.f, 0.f, 0.f, 0.f};
-        __syncthreads();
-        // stage Theta^T[c0 .. c0+127][kc .. kc+kn) (zeros past Fo), 16 B per thread and step
-        const int per_row = kn / 4;
-        for (int i = threadIdx.x; i < kCols * per_row; i += kBlock) {
-            const int n = i / per_row, q = i % per_row;
+        for (int i = 0; i < SB; ++i) {
+            const int q = threadIdx.x + i * kBlock;
+            const int64_t k = kc + q / (COLS / 4), c = c0 + 4 * (q % (COLS / 4));
             f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (c0 + n < Fo) v = *reinterpret_cast<const f32x4 *>(tt + (c0 + n) * Kp + kc + 4 * q);
-            *reinterpret_cast<f32x4 *>(lds + n * kLdsStrideF + 4 * q) = v;
-        }
-        __syncthreads();
+            if (k < Fi) {
+                const float *t = theta + k * Fo + c;
+                if (tvec && c + 4 <= Fo) {
+                    v = *reinterpret_cast<const f32x4 *>(t);
+                } else {
 #pragma unroll
-        for (int st = 0; st < kChunkF / 16; ++st) {
-            if (st * 16 >= kn) break;
-            // all eight Theta^T operands first, then the steps e outermost: the 16
-            // accumulators are updated in turn, so no MFMA waits on the one before
-            f32x4 b[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                b[u] = *reinterpret_cast<const f32x4 *>(lds + (16 * u + li) * kLdsStrideF + 16 * st + 4 * lg);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    acc[0][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[u][e], a[0][st][e], acc[0][u], 0, 0, 0);
-                    acc[1][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[u][e], a[1][st][e], acc[1][u], 0, 0, 0);
+                    for (int j = 0; j < 4; ++j) v[j] = c + j < Fo ? t[j] : 0.f;
                 }
+            }
+            b[i] = v;
         }
+    };
+    f32x4 acc[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 a[SA], an[SA], b[SB];
+    load_x(0, a);
+    load_theta(0, b);
+    int buf = 0;
+    for (int64_t kc = 0; kc < Fi; kc += KC, buf ^= 1) {
+#pragma unroll
+        for (int i = 0; i < SB; ++i) {
+            const int q = threadIdx.x + i * kBlock;
+            *reinterpret_cast<f32x4 *>(&lds[buf][(q / (COLS / 4)) * CS + 4 * (q % (COLS / 4))]) = b[i];
+        }
+        // one barrier a stage: a buffer is written again two stages on, after
+        // every wavefront has passed the barrier of the stage between
+        __syncthreads();
+        if (kc + KC < Fi) {
+            load_x(kc + KC, an);
+            load_theta(kc + KC, b);
+        }
+#pragma unroll
+        for (int st = 0; st < SA; ++st) {
+            if (kc + 16 * st >= Fi) break;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float *t = &lds[buf][(16 * st + 4 * lg + e) * CS + cw + li];
+#pragma unroll
+                for (int u = 0; u < NU; ++u)
+                    acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(t[16 * u], a[st][e], acc[u], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int st = 0; st < SA; ++st) a[st] = an[st];
     }
-    store_tile(out, N, Fo, r0, c0, li, lg, acc);
+    if (row >= N) return;
+    const bool vec = Fo % 4 == 0 && (reinterpret_cast<uintptr_t>(out) & (4 * sizeof(TO) - 1)) == 0;
+#pragma unroll
+    for (int u = 0; u < NU; ++u) store4(out, row, c0 + cw + 16 * u + 4 * lg, Fo, acc[u], vec);
+}
+
+template <typename TO, int NU, int WC, int KC>
+int launch_dense_f32(const float *x, int64_t N, int64_t Fi, const float *theta, int64_t Fo, TO *out, bool vec,
+                     hipStream_t s) {
+    constexpr int64_t rows = 16 * (kBlock / kWave / WC), cols = 16 * NU * WC;
+    const dim3 grid(static_cast<unsigned>((N + rows - 1) / rows), static_cast<unsigned>((Fo + cols - 1) / cols));
+    const bool tvec = Fo % 4 == 0 && (reinterpret_cast<uintptr_t>(theta) & 15) == 0;
+    if (vec) k_dense_f32<TO, true, NU, WC, KC><<<grid, kBlock, 0, s>>>(x, N, Fi, theta, Fo, tvec, out);
+    else k_dense_f32<TO, false, NU, WC, KC><<<grid, kBlock, 0, s>>>(x, N, Fi, theta, Fo, tvec, out);
+    PYG_LAUNCH_CHECK();
+    return PYG_OK;
+}
+
+// Columns of a workgroup: as few as hold Theta's, up to 128.
+template <typename TO>
+int dense_f32(const float *x, int64_t N, int64_t Fi, const float *theta, int64_t Fo, TO *out, bool vec, hipStream_t s) {
+    if (Fo <= 16) return launch_dense_f32<TO, 1, 1, 64>(x, N, Fi, theta, Fo, out, vec, s);
+    if (Fo <= 32) return launch_dense_f32<TO, 2, 1, 64>(x, N, Fi, theta, Fo, out, vec, s);
+    if (Fo <= 64) return launch_dense_f32<TO, 2, 2, 64>(x, N, Fi, theta, Fo, out, vec, s);
+    return launch_dense_f32<TO, 4, 2, 32>(x, N, Fi, theta, Fo, out, vec, s);
 }
 
 // Fi <= 128: persistent workgroups that stage the whole Theta^T (128 columns
@@ -419,17 +474,17 @@ extern "C" int pyg_dense_transform(const void *x, int x_dtype, int64_t N, int64_
     if (ob < xb + N * Fi * xsz && xb < ob + N * Fo * osz) return PYG_ERR_INVALID_ARG;  // out overlaps x
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (x_dtype == PYG_F32) {
-        const int64_t Kp = kpadf(Fi), Fp = fopad(Fo);
-        float *tt = static_cast<float *>(ws);
-        k_theta_t_f32<<<grid_for(Fp * Kp, kBlock * 4), kBlock, 0, s>>>(static_cast<const float *>(theta), Fi, Fo, Kp, Fp,
-                                                                       tt);
-        PYG_LAUNCH_CHECK();
         const bool vec = Fi % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0;
+        const float *xf = static_cast<const float *>(x), *th = static_cast<const float *>(theta);
         const int64_t nblocks = (N + kRowsWave * (kBlock / kWave) - 1) / (kRowsWave * (kBlock / kWave));
-        const unsigned gy = static_cast<unsigned>((Fo + kCols - 1) / kCols);
-        const dim3 grid(static_cast<unsigned>(nblocks), gy);
-        const float *xf = static_cast<const float *>(x);
-        if (Kp <= 128 && PYG_DENSE_F32_PERSIST) {  // persistent workgroups, Theta staged once
+        // persistent workgroups with the whole Theta^T staged once: K of one
+        // stage, columns for its 128-column tiles and two rounds of row blocks
+        if (Fi <= 128 && Fo > 64 && nblocks >= PYG_DENSE_F32_PERSIST * kPersistBlocksF) {
+            const int64_t Kp = kpadf(Fi), Fp = fopad(Fo);
+            float *tt = static_cast<float *>(ws);
+            k_theta_t_f32<<<grid_for(Fp * Kp, kBlock * 4), kBlock, 0, s>>>(th, Fi, Fo, Kp, Fp, tt);
+            PYG_LAUNCH_CHECK();
+            const unsigned gy = static_cast<unsigned>((Fo + kCols - 1) / kCols);
             const int64_t iters = (nblocks + kPersistBlocksF - 1) / kPersistBlocksF;
             const dim3 g(static_cast<unsigned>((nblocks + iters - 1) / iters), gy);
             if (out_dtype == PYG_F32) {
@@ -442,15 +497,8 @@ extern "C" int pyg_dense_transform(const void *x, int x_dtype, int64_t N, int64_
             PYG_LAUNCH_CHECK();
             return PYG_OK;
         }
-        if (out_dtype == PYG_F32) {
-            if (vec) k_dense_f32<float, true><<<grid, kBlock, 0, s>>>(xf, N, Fi, Kp, tt, Fo, static_cast<float *>(out));
-            else k_dense_f32<float, false><<<grid, kBlock, 0, s>>>(xf, N, Fi, Kp, tt, Fo, static_cast<float *>(out));
-        } else {
-            if (vec) k_dense_f32<uint16_t, true><<<grid, kBlock, 0, s>>>(xf, N, Fi, Kp, tt, Fo, static_cast<uint16_t *>(out));
-            else k_dense_f32<uint16_t, false><<<grid, kBlock, 0, s>>>(xf, N, Fi, Kp, tt, Fo, static_cast<uint16_t *>(out));
-        }
-        PYG_LAUNCH_CHECK();
-        return PYG_OK;
+        return out_dtype == PYG_F32 ? dense_f32(xf, N, Fi, th, Fo, static_cast<float *>(out), vec, s)
+                                    : dense_f32(xf, N, Fi, th, Fo, static_cast<uint16_t *>(out), vec, s);
     }
     const int64_t Kp = kpad(Fi), Fp = fopad(Fo);
     uint16_t *tt = static_cast<uint16_t *>(ws);
