@@ -216,6 +216,13 @@ constexpr int kSegMsgEdgeReluGrad = 100;
 constexpr int kSegMsgGcn = 101;
 int64_t segment_chunk(int64_t E, int64_t n_rows, int64_t requested);
 
+// Chunks one wavefront of a fold launch looks at: enough wavefronts first.
+constexpr int kFoldPerMax = 16;
+static inline int fold_per(int64_t nchunks) {
+    const int64_t per = nchunks / 8192;
+    return per < 1 ? 1 : per > kFoldPerMax ? kFoldPerMax : static_cast<int>(per);
+}
+
 // Folds the pieces of the long rows (sum): part [2 * nchunks, F] and head_row
 // [nchunks] as the segment kernel's walk writes them.
 int segment_fold_pieces(const int64_t *rowptr, int64_t n_rows, int64_t E, int64_t F, int64_t chunk, int32_t *head_row,
@@ -241,6 +248,12 @@ size_t segment_blocked_workspace(int64_t E, int64_t n_rows, int64_t F, int64_t B
 int segment_reduce_blocked(const SegmentArgs &a, int64_t B, void *ws, size_t ws_bytes, hipStream_t s);
 size_t segment_workspace(int64_t E, int64_t F, int aggr, int64_t chunk, int64_t n_rows);
 int segment_reduce(const SegmentArgs &a, void *ws, size_t ws_bytes, hipStream_t s);
+
+// The plain CSR of a small edge list in one launch (no workspace); w_out is
+// written when w is given.
+bool small_csr_ok(int64_t E, int64_t N);
+int small_csr(const int64_t *src, const int64_t *dst, int64_t E, int64_t N, const float *w, int64_t *rowptr,
+              int32_t *col, int64_t *perm, float *w_out, hipStream_t s);
 
 // Both gradients of a weighted (msg PYG_MSG_SRC) or edge-feature propagate in
 // one pass over the reversed CSR (sum; mean with rows g already scaled).

@@ -701,8 +701,19 @@ __global__ __launch_bounds__(kBlock) void k_row_bounds_low(const uint16_t *__res
 
 __global__ void k_gather_edges(const int64_t *__restrict__ perm, int64_t E, const float *__restrict__ in,
                                float *__restrict__ out) {
-    for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < E; p += (int64_t)gridDim.x * blockDim.x)
-        out[p] = in[perm[p]];
+    constexpr int U = 4;  // gathers in flight per thread
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t p0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p0 < E; p0 += U * step) {
+        int64_t k[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) k[u] = p0 + u * step < E ? __builtin_nontemporal_load(perm + p0 + u * step) : 0;
+        float v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = p0 + u * step < E ? in[k[u]] : 0.f;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (p0 + u * step < E) out[p0 + u * step] = v[u];
+    }
 }
 
 __global__ void k_validate_coo(const int64_t *__restrict__ ei, int64_t n, int64_t N, unsigned long long *__restrict__ bad) {
@@ -1023,6 +1034,9 @@ int coo_to_csr_impl(const int64_t *edge_index, int64_t E, int64_t N, int64_t B, 
     if (E == 0) return fill<int64_t>(rowptr, rows + 1, 0, s);
     const int64_t *src = edge_index;
     const int64_t *dst = edge_index + E;
+    // few edges: the passes below are eight launches of latency
+    if (B == 1 && small_csr_ok(E, N))
+        return small_csr(src, dst, E, N, weight_csr ? edge_weight : nullptr, rowptr, col, perm, weight_csr, s);
 
     const int64_t ntiles = (E + kTile - 1) / kTile;
     Packing pk;

@@ -1,0 +1,39 @@
+"""The one-launch CSR of small edge lists, bit for bit against the oracle's:
+ragged groups of 64 edges and 64 targets, the ends of its range and one past
+each, one target with every edge, empty targets, weights."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from tests.parity import to_dev
+
+pytestmark = pytest.mark.gpu
+
+# (N, E): the range ends at 16,384 nodes and 24,576 edges
+CASES = [(1, 1), (63, 64), (64, 65), (65, 1000), (3200, 14081), (16384, 24576), (16385, 24576), (16384, 24577),
+         (5000, 7), (700, 24575)]
+
+
+@pytest.mark.parametrize("kind", ["random", "star", "last"])
+@pytest.mark.parametrize("case", CASES)
+def test_small_csr_bits(case, kind):
+    import paper_1903_02428_amd as pyg
+    N, E = case
+    rng = np.random.default_rng(7000 + N + E)
+    ei = synth.random_coo(rng, N, E)
+    if kind == "star":
+        ei[1] = N // 2
+    elif kind == "last":
+        ei[1] = N - 1 - (ei[1] % min(N, 3))
+    w = rng.standard_normal(E).astype(np.float32)
+    csr = pyg.coo_to_csr(to_dev(ei), N, to_dev(w))
+    plain = pyg.coo_to_csr(to_dev(ei), N)
+    torch.cuda.synchronize()
+    rowptr, col, perm = oracle.coo_to_csr(ei, N)
+    for c in (csr, plain):
+        assert np.array_equal(c.rowptr.cpu().numpy(), rowptr)
+        assert np.array_equal(c.perm.cpu().numpy(), perm)
+        assert np.array_equal(c.col.cpu().numpy(), col)
+    assert np.array_equal(csr.weight.cpu().numpy(), w[perm])
