@@ -182,27 +182,43 @@ __global__ __launch_bounds__(kBlock) void k_sddmm_vec(const T *__restrict__ g, c
     }
 }
 
-// Max: route every output element's gradient to its winning edge; grad_w
-// entries at the edge id k, or at its CSR slot inv[k] (CSR order).
-template <typename T, bool DIFF>
+// Difference messages under max: what a node's own rows give back, -g where
+// the row has a winner. It is the accumulator's first value, so that only the
+// winners' sources take an atomic (the device completes about 20G atomic
+// requests a second; half of them were these).
+template <typename T>
+__global__ void k_max_self(const T *__restrict__ g, int64_t NF, int64_t E, const int64_t *__restrict__ argmax,
+                           float *__restrict__ acc) {
+    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < NF; t += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t k = argmax[t];
+        acc[t] = (k >= 0 && k < E) ? -ld(g, t) : 0.f;
+    }
+}
+
+// Max: route every output element's gradient to its winning edge's source;
+// grad_w entries at the edge id k, or at its CSR slot inv[k] (CSR order).
+template <typename T>
 __global__ void k_max_backward(const T *__restrict__ g, const T *__restrict__ x, int64_t N, int64_t F,
                                const int64_t *__restrict__ ei, int64_t E, const float *__restrict__ w,
                                const int64_t *__restrict__ argmax, const int32_t *__restrict__ inv,
                                float *__restrict__ acc, float *__restrict__ grad_w) {
-    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < N * F; t += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t k = argmax[t];
-        if (k < 0 || k >= E) continue;  // empty row (sentinel E)
-        const int64_t i = t / F, f = t - i * F;
-        const int64_t j = ei[k];
-        const float gv = ld(g, t);
-        if constexpr (DIFF) {
-            unsafeAtomicAdd(&acc[j * F + f], gv);
-            unsafeAtomicAdd(&acc[i * F + f], -gv);
-        } else {
-            unsafeAtomicAdd(&acc[j * F + f], w ? w[k] * gv : gv);
+    constexpr int U = 4;  // winner -> source chains in flight per thread
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t t0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t0 < N * F; t0 += U * step) {
+        int64_t k[U], j[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) k[u] = t0 + u * step < N * F ? argmax[t0 + u * step] : -1;  // -1 or E: none
+#pragma unroll
+        for (int u = 0; u < U; ++u) j[u] = (k[u] >= 0 && k[u] < E) ? ei[k[u]] : -1;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (j[u] < 0) continue;
+            const int64_t t = t0 + u * step, f = t % F;
+            const float gv = ld(g, t);
+            unsafeAtomicAdd(&acc[j[u] * F + f], w ? w[k[u]] * gv : gv);
             if (grad_w) {
-                const int64_t wk = inv ? inv[k] : k;
-                if (wk >= 0 && wk < E) unsafeAtomicAdd(&grad_w[wk], gv * ld(x, j * F + f));
+                const int64_t wk = inv ? inv[k[u]] : k[u];
+                if (wk >= 0 && wk < E) unsafeAtomicAdd(&grad_w[wk], gv * ld(x, j[u] * F + f));
             }
         }
     }
@@ -273,19 +289,21 @@ int backward_typed(const void *grad_out, const void *x, int dtype, int64_t N, in
     if (grad_w) PYG_TRY(fill<float>(grad_w, E, 0.f, s));
     if (aggr == PYG_MAX) {
         float *acc = sizeof(T) == 4 ? static_cast<float *>(grad_x) : w.acc;
-        PYG_TRY(fill<float>(acc, NF, 0.f, s));
+        const bool diff = msg == PYG_MSG_DIFF;  // never weighted
+        if (diff && E > 0) {
+            k_max_self<T><<<grid_for(NF, kBlock * 4), kBlock, 0, s>>>(g, NF, E, argmax, acc);
+            PYG_LAUNCH_CHECK();
+        } else {
+            PYG_TRY(fill<float>(acc, NF, 0.f, s));
+        }
         if (E > 0) {
             const int32_t *inv = nullptr;
             if (grad_w && w_csr) {
                 PYG_TRY(inverse_perm(csr->perm, E, w.inv, s));
                 inv = w.inv;
             }
-            if (msg == PYG_MSG_DIFF)
-                k_max_backward<T, true><<<grid_for(NF, kBlock * 4), kBlock, 0, s>>>(g, static_cast<const T *>(x), N, F, ei, E,
-                                                                                     ew, argmax, nullptr, acc, nullptr);
-            else
-                k_max_backward<T, false><<<grid_for(NF, kBlock * 4), kBlock, 0, s>>>(g, static_cast<const T *>(x), N, F, ei, E,
-                                                                                      ew, argmax, inv, acc, grad_w);
+            k_max_backward<T><<<grid_for(NF, kBlock * 4), kBlock, 0, s>>>(g, static_cast<const T *>(x), N, F, ei, E, ew,
+                                                                         argmax, inv, acc, grad_w);
             PYG_LAUNCH_CHECK();
         }
         if (sizeof(T) == 2) {

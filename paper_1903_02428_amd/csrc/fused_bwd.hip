@@ -15,9 +15,11 @@
 // the segment kernel's order for the sums (the same bits as its whole rows).
 //
 // Measured on a power-law graph of 100,000 nodes and 2M edges: both gradients
-// of the weighted sum (fp32, F = 100) 657 us in two passes, 206 us in one; of
-// max(x_j + e, 0) (bf16, F = 64) 709 and 279 us. What is left is latency (rows
-// of 20 slots) rather than bytes: 100 MB and 550 MB.
+// of the weighted sum (fp32, F = 100) 657 us in two passes, 180 us in one; of
+// max(x_j + e, 0) (bf16, F = 64) 709 and 175 us. What is left is latency (rows
+// of 20 slots) rather than bytes (100 and 550 MB): fewer slots in flight per
+// lane and more wavefronts are faster (weights 8, 4, 2 slots: 199, 175, 195 us;
+// edge features 8, 4, 2: 294, 200, 167 us).
 #include "rows.hpp"
 
 namespace pyg {
@@ -50,6 +52,13 @@ struct FusedBackward {
     using R = typename LN::R;
     static constexpr int EP = LN::N;
     static constexpr bool EDGE = KIND != kWeight;
+    template <typename TE> using Share = typename std::conditional<sizeof(TE) == 4 || EP == 8, uint4, uint2>::type;
+    template <typename TE>
+    __device__ static __forceinline__ float share_get(const Share<TE> &r, int e) {
+        const uint32_t *w = reinterpret_cast<const uint32_t *>(&r);
+        if constexpr (sizeof(TE) == 4) return __uint_as_float(w[e]);
+        else return __uint_as_float((e & 1) ? w[e >> 1] & 0xFFFF0000u : w[e >> 1] << 16);
+    }
     const FusedParams &p;
     int lane, L, S, q, sg, hot;
     int64_t f0;
@@ -71,13 +80,12 @@ struct FusedBackward {
     __device__ __forceinline__ void take(const int (&jj)[U], const bool (&ok)[U], const float (&ww)[U],
                                          const int (&ee)[U]) {
         R v[U];
-        float ev[EDGE ? U : 1][EP];
+        Share<T> ev[EDGE ? U : 1];  // raw: a lane's share of the edge row
         if constexpr (KIND == kRelu || KIND == kMul) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-#pragma unroll
-                for (int e = 0; e < EP; ++e) ev[u][e] = 0.f;
-                if (ok[u] && act) ldv<T, EP>(static_cast<const T *>(p.ea) + (int64_t)ee[u] * p.F + f0, ev[u]);
+                if (ok[u] && act) ev[u] = *reinterpret_cast<const Share<T> *>(static_cast<const T *>(p.ea) + (int64_t)ee[u] * p.F + f0);
+                else ev[u] = Share<T>{};
             }
         }
 #pragma unroll
@@ -118,10 +126,10 @@ struct FusedBackward {
                 for (int e = 0; e < EP; ++e) {
                     const float gv = LN::get(v[u], e);
                     float c = gv;  // what grad x_j receives (0 where there is no slot: v is 0)
-                    if constexpr (KIND == kRelu) c = xo[e] + ev[u][e] > 0.f ? gv : 0.f;
+                    if constexpr (KIND == kRelu) c = xo[e] + share_get<T>(ev[u], e) > 0.f ? gv : 0.f;
                     if constexpr (KIND == kMul) {
                         o[e] = gv * xo[e];
-                        acc[e] = fmaf(gv, ev[u][e], acc[e]);
+                        acc[e] = fmaf(gv, share_get<T>(ev[u], e), acc[e]);
                     } else {
                         o[e] = c;
                         acc[e] += c;
@@ -230,7 +238,7 @@ FusedWs carve_fused(void *base, int64_t N, int64_t F, int64_t E, int64_t chunk) 
 
 template <typename TG, typename T, int KIND>
 int launch_fused(const FusedParams &p, hipStream_t s) {
-    constexpr int U = KIND == kWeight ? 8 : 4;
+    constexpr int U = KIND == kWeight ? 4 : 2;  // slots in flight per lane: registers, and with them wavefronts, count for more
     const unsigned grid = static_cast<unsigned>((p.zero_items + p.walk.nchunks + 3) / 4);
     // rows of at most 16 slots on average go to sub-groups, as in the segment kernel
     if (p.lg < 6 && p.walk.E <= 16 * p.walk.N)

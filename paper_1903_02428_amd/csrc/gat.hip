@@ -23,13 +23,13 @@
 //             grad x_j = sum alpha g_i, <g_i, x_j> with x_j held in registers,
 //             and grad a_src[j] = sum dv.
 // Measured there (fp32, forward and backward): 35.0 ms by the separate kernels,
-// 17.3 ms by these (8.2 ms forward, 8.9 ms reversed pass), both bound by the
+// 17.0 ms by these (8.0 ms forward, 8.9 ms reversed pass), both bound by the
 // rate of cache lines past L2 (five lines gathered per slot and direction; 2,
 // 4 or 8 slots in flight per lane take the same time). Windows of 8 or 16
 // lanes per slot lose (22.0 and 18.9 ms: the scores and the table are gathered
 // again for every window), the non-temporal hint for rows that are no hubs
 // gains (18.0 to 17.3 ms). A 108k-edge graph (8 heads of 8): 16 launches and
-// 214 us of kernels become 5 and 73 us.
+// 214 us of kernels become 5 and 58 us.
 // All sums run in fixed orders: deterministic. Heads never straddle a lane's
 // 16-byte vector; other shapes take the separate softmax and sum kernels.
 #include "rows.hpp"
@@ -259,16 +259,15 @@ __global__ __launch_bounds__(kBlock) void k_gat_forward(GatParams p) {
     else walk_heavy(p.walk, c, lane, op);
 }
 
-// The pieces of every long row, in chunk order: their common maximum, then
-// the rescaled sums. One wavefront looks at kFoldChunks chunks and takes the
+// The pieces of every long row, in chunk order, rescaled to the maximum so far. One wavefront looks at `per` chunks and takes the
 // long rows that start in them, a lane per feature.
 template <typename T, bool GRAD>
-__global__ __launch_bounds__(kBlock) void k_gat_fold(GatParams p) {
+__global__ __launch_bounds__(kBlock) void k_gat_fold(GatParams p, int per) {
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t w = uniform64((int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave);
-    const int64_t c0 = w * kFoldChunks;
+    const int64_t c0 = w * per;
     if (c0 >= p.walk.nchunks) return;
-    const int32_t mine = (lane < kFoldChunks && c0 + lane < p.walk.nchunks) ? p.walk.head_row[c0 + lane] : -1;
+    const int32_t mine = (lane < per && c0 + lane < p.walk.nchunks) ? p.walk.head_row[c0 + lane] : -1;
     uint64_t hit = __ballot(mine >= 0);
     const int64_t C = p.F / p.H;
     while (hit) {
@@ -278,18 +277,33 @@ __global__ __launch_bounds__(kBlock) void k_gat_fold(GatParams p) {
         const int64_t K = (uniform64(p.walk.rowptr[r + 1]) - 1) / p.walk.chunk - c + 1;
         for (int64_t f = lane; f < p.F; f += kWave) {
             const int64_t h = f / C;
-            float m = -INFINITY;
-            for (int64_t i = 0; i < K; ++i) m = fmaxf(m, p.part_st[piece_of(c, i) * p.H + h].x);
-            float z = 0.f, zp = 0.f, a = 0.f, b = 0.f;
-#pragma unroll 4
-            for (int64_t i = 0; i < K; ++i) {
-                const int64_t sl = piece_of(c, i);
-                const float4 st = p.part_st[sl * p.H + h];
-                const float s = pexp(st.x, m);
-                z = fmaf(s, st.y, z);
-                zp = fmaf(s, st.z, zp);
-                a = fmaf(s, p.part[sl * p.F + f], a);
-                if constexpr (GRAD) b = fmaf(s, p.part_plus[sl * p.F + f], b);
+            float m = -INFINITY, z = 0.f, zp = 0.f, a = 0.f, b = 0.f;
+            for (int64_t i0 = 0; i0 < K; i0 += 4) {  // four pieces in flight
+                float4 st[4];
+                float pa[4], pb[4];
+                float mx = m;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int64_t sl = piece_of(c, i0 + u);
+                    const bool on = i0 + u < K;
+                    st[u] = on ? p.part_st[sl * p.H + h] : make_float4(-INFINITY, 0.f, 0.f, 0.f);
+                    pa[u] = on ? p.part[sl * p.F + f] : 0.f;
+                    if constexpr (GRAD) pb[u] = on ? p.part_plus[sl * p.F + f] : 0.f;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) mx = fmaxf(mx, st[u].x);
+                const float s0 = pexp(m, mx);
+                z *= s0, zp *= s0, a *= s0;
+                if constexpr (GRAD) b *= s0;
+                m = mx;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const float s = pexp(st[u].x, m);
+                    z = fmaf(s, st[u].y, z);
+                    zp = fmaf(s, st[u].z, zp);
+                    a = fmaf(s, pa[u], a);
+                    if constexpr (GRAD) b = fmaf(s, pb[u], b);
+                }
             }
             const float inv = 1.f / z;
             if constexpr (sizeof(T) == 2) static_cast<T *>(p.out)[r * p.F + f] = f32_to_bf16_rne(a * inv);
@@ -480,12 +494,12 @@ __global__ __launch_bounds__(kBlock) void k_gat_backward(GatParams p) {
 }
 
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_gat_backward_fold(GatParams p) {
+__global__ __launch_bounds__(kBlock) void k_gat_backward_fold(GatParams p, int per) {
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t w = uniform64((int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave);
-    const int64_t c0 = w * kFoldChunks;
+    const int64_t c0 = w * per;
     if (c0 >= p.walk.nchunks) return;
-    const int32_t mine = (lane < kFoldChunks && c0 + lane < p.walk.nchunks) ? p.walk.head_row[c0 + lane] : -1;
+    const int32_t mine = (lane < per && c0 + lane < p.walk.nchunks) ? p.walk.head_row[c0 + lane] : -1;
     uint64_t hit = __ballot(mine >= 0);
     while (hit) {
         const int k = __ffsll(static_cast<unsigned long long>(hit)) - 1;
@@ -588,7 +602,8 @@ int launch_forward(const GatParams &p, hipStream_t s) {
     else k_gat_forward<T, U, GRAD, false><<<grid, kBlock, 0, s>>>(p);
     PYG_LAUNCH_CHECK();
     if (p.walk.nchunks > 1) {
-        k_gat_fold<T, GRAD><<<grid_for(p.walk.nchunks, 4 * kFoldChunks), kBlock, 0, s>>>(p);
+        const int per = fold_per(p.walk.nchunks);
+        k_gat_fold<T, GRAD><<<grid_for(p.walk.nchunks, 4 * per, 1 << 26), kBlock, 0, s>>>(p, per);
         PYG_LAUNCH_CHECK();
     }
     return PYG_OK;
@@ -609,7 +624,8 @@ int launch_backward(const GatParams &p, const float *all, const float *plus, con
     else k_gat_backward<T, U, false><<<grid, kBlock, 0, s>>>(p);
     PYG_LAUNCH_CHECK();
     if (p.walk.nchunks > 1) {
-        k_gat_backward_fold<T><<<grid_for(p.walk.nchunks, 4 * kFoldChunks), kBlock, 0, s>>>(p);
+        const int per = fold_per(p.walk.nchunks);
+        k_gat_backward_fold<T><<<grid_for(p.walk.nchunks, 4 * per, 1 << 26), kBlock, 0, s>>>(p, per);
         PYG_LAUNCH_CHECK();
     }
     return PYG_OK;

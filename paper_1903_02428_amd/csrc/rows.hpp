@@ -174,7 +174,4 @@ __device__ __forceinline__ void each_empty_row(const int64_t *rowptr, int64_t N,
 // The slot of piece m of the long row whose head chunk is c.
 __device__ __forceinline__ int64_t piece_of(int64_t c, int64_t m) { return m == 0 ? 2 * c + 1 : 2 * (c + m); }
 
-// Chunks looked at by one wavefront of a fold launch.
-constexpr int kFoldChunks = 16;
-
 }  // namespace pyg

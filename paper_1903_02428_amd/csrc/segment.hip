@@ -237,6 +237,10 @@ __device__ __forceinline__ void reduce_piece(const SegParams &p, int64_t r, int6
         }
         if constexpr (MSG == kMsgWeighted) w = __builtin_nontemporal_load(p.w + e);
         if constexpr (MSG == kMsgHeads) ar = p.alpha_idx ? __builtin_nontemporal_load(p.alpha_idx + e) : static_cast<int>(e);
+        // the edge row of the slot, with the column: a load less in the chain before its features
+        if constexpr (MSG >= kMsgEdgeAdd && MSG <= kMsgEdgeReluGrad)
+            ar = p.ea_idx ? __builtin_nontemporal_load(p.ea_idx + e)
+                          : p.ea_perm ? static_cast<int>(__builtin_nontemporal_load(p.ea_perm + e)) : static_cast<int>(e);
     };
     int nxc = 0, nxa = 0;
     float nxw = 1.f;
@@ -257,7 +261,8 @@ __device__ __forceinline__ void reduce_piece(const SegParams &p, int64_t r, int6
                 ok[u] = idx < n;
                 jj[u] = __shfl(myc, idx & (kWave - 1), kWave);
                 if constexpr (kWeightedMsg<MSG>) ww[u] = __shfl(myw, idx & (kWave - 1), kWave);
-                if constexpr (MSG == kMsgHeads) aa[u] = __shfl(mya, idx & (kWave - 1), kWave);
+                if constexpr (MSG == kMsgHeads || (MSG >= kMsgEdgeAdd && MSG <= kMsgEdgeReluGrad))
+                    aa[u] = __shfl(mya, idx & (kWave - 1), kWave);
             }
             float wh[U][NS];
             if constexpr (MSG == kMsgHeads) {
@@ -267,19 +272,16 @@ __device__ __forceinline__ void reduce_piece(const SegParams &p, int64_t r, int6
                     for (int sl = 0; sl < NS; ++sl)
                         wh[u][sl] = (ok[u] && act[sl]) ? p.alpha[(int64_t)aa[u] * p.H + hd[sl]] : 0.f;
             }
-            constexpr bool EDGE = MSG >= kMsgEdgeAdd;
+            constexpr bool EDGE = MSG >= kMsgEdgeAdd && MSG <= kMsgEdgeReluGrad;
             R ev[U][NS];
             if constexpr (EDGE) {  // edge rows stream once: non-temporal
 #pragma unroll
                 for (int u = 0; u < U; ++u)
 #pragma unroll
                     for (int sl = 0; sl < NS; ++sl) {
-                        const int64_t slot = base + st + u * S + sg;
                         ev[u][sl] = LN::zero();
-                        if (ok[u] && act[sl]) {
-                            const int64_t er = p.ea_idx ? p.ea_idx[slot] : (p.ea_perm ? p.ea_perm[slot] : slot);
-                            ev[u][sl] = LN::load_nt(static_cast<const T *>(p.ea) + er * p.F + f0[sl]);
-                        }
+                        if (ok[u] && act[sl])
+                            ev[u][sl] = LN::load_nt(static_cast<const T *>(p.ea) + (int64_t)aa[u] * p.F + f0[sl]);
                     }
             }
             R v[U][NS];
@@ -431,7 +433,7 @@ __device__ __forceinline__ void light_row(const SegParams &p, int64_t r, int64_t
                 ww[u] = (ok[u] && act) ? p.alpha[ar * p.H + hd] : 0.f;
             }
         }
-        constexpr bool EDGE = MSG >= kMsgEdgeAdd;
+        constexpr bool EDGE = MSG >= kMsgEdgeAdd && MSG <= kMsgEdgeReluGrad;
         R ev[U];
         if constexpr (EDGE) {
 #pragma unroll
@@ -750,11 +752,11 @@ __global__ __launch_bounds__(kBlock) void k_segment_fold_groups(SegParams p) {
         fold_long_row<T, MAXA, kBlock / kWave, 8, OF32, false>(p, c, r2, sv, sp, 0, 1, kFoldGroup);
 }
 
-// The fold proper: one workgroup per chunk that starts a long row. GROUPED
-// (after k_segment_fold_groups): a row of more than kFoldGroup pieces folds
-// its groups' partials, pieces 0, kFoldGroup, 2 kFoldGroup, ... in order.
-template <typename T, bool MAXA, int WAVES, bool OF32, bool GROUPED>
-__global__ __launch_bounds__(WAVES * kWave) void k_segment_fixup(SegParams p) {
+// Level 2: one workgroup per chunk that starts a long row; a row of more
+// than kFoldGroup pieces folds its groups' partials, pieces 0, kFoldGroup,
+// 2 kFoldGroup, ... in order.
+template <typename T, bool MAXA, int WAVES, bool OF32>
+__global__ __launch_bounds__(WAVES * kWave) void k_segment_fixup_grouped(SegParams p) {
     constexpr int kW = WAVES;
     constexpr int kU = WAVES > 4 ? 16 : 8;
     __shared__ float sv[kW][kWave];
@@ -764,8 +766,78 @@ __global__ __launch_bounds__(WAVES * kWave) void k_segment_fixup(SegParams p) {
     const int64_t r = p.head_row[c];
     if (r < 0) return;  // uniform over the workgroup
     const int64_t K = (p.rowptr[r + 1] - 1) / p.chunk - c + 1;
-    if (GROUPED && K > kFoldGroup) fold_long_row<T, MAXA, kW, kU, OF32>(p, c, r, sv, sp, 0, kFoldGroup);
+    if (K > kFoldGroup) fold_long_row<T, MAXA, kW, kU, OF32>(p, c, r, sv, sp, 0, kFoldGroup);
     else fold_long_row<T, MAXA, kW, kU, OF32>(p, c, r, sv, sp);
+}
+
+// The fold of ordinary graphs. A wavefront looks at `per` chunks at once (a
+// lane each) and folds the long rows that start in them one after another, a
+// lane per feature and eight pieces in flight; a row of more than kFoldGroup
+// pieces is left to the whole workgroup afterwards. One workgroup per chunk,
+// nearly all of them with nothing to fold, took 44 us on the large power-law
+// graph's 112,000 chunks; with 16 chunks per wavefront 25 us. Graphs of few chunks
+// keep a wavefront per chunk (fold_per in common.hpp).
+template <typename T, bool MAXA, bool OF32>
+__global__ __launch_bounds__(kBlock) void k_segment_fixup(SegParams p, int per) {
+    constexpr int kW = kBlock / kWave;
+    __shared__ float sv[kW][kWave];
+    __shared__ int32_t sp[kW][kWave];
+    __shared__ int32_t big_row[kW * kFoldPerMax];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int64_t c0 = ((int64_t)blockIdx.x * kW + wave) * per;
+    int32_t row = -1, K = 0;
+    if (lane < per && c0 + lane < p.nchunks) {
+        row = p.head_row[c0 + lane];
+        if (row >= 0) K = static_cast<int32_t>((p.rowptr[row + 1] - 1) / p.chunk - (c0 + lane) + 1);
+    }
+    const bool big = K > kFoldGroup;
+    if (lane < per) big_row[wave * per + lane] = big ? row : -1;
+    uint64_t hit = __ballot(row >= 0 && !big);
+    T *out = static_cast<T *>(p.out);
+    while (hit) {
+        const int k = __ffsll(static_cast<unsigned long long>(hit)) - 1;
+        hit &= hit - 1;
+        const int64_t c = c0 + k, r = __builtin_amdgcn_readlane(row, k);
+        const int n = __builtin_amdgcn_readlane(K, k);
+        for (int64_t f = p.fbase + lane; f < p.fbase + p.fcnt; f += kWave) {
+            // sums in four ranges of the pieces, then over the ranges: the order
+            // (and the shorter rounding chains) of a workgroup's four waves
+            float v = 0.f, total = 0.f;
+            int range = 0;
+            int32_t ps = -1;
+            for (int m = 0; m < n; m += 8) {
+                float o[8];
+                int32_t op[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int64_t i = piece_slot(c, m + u) * p.F + f;
+                    o[u] = m + u < n ? p.part_val[i] : 0.f;
+                    if constexpr (MAXA) op[u] = m + u < n ? p.part_pos[i] : -1;
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    if (m + u >= n) break;
+                    if constexpr (MAXA) {
+                        if (ps < 0 || o[u] > v) v = o[u], ps = op[u];  // strict: the earliest piece keeps a tie
+                    } else {
+                        for (; m + u >= n * (range + 1) / kW; ++range) total += v, v = 0.f;
+                        v += o[u];
+                    }
+                }
+            }
+            if constexpr (!MAXA) v += total;
+            if (!MAXA && p.mean) v = v / static_cast<float>(p.rowptr[r + 1] - p.rowptr[r]);
+            if constexpr (OF32) static_cast<float *>(p.out)[r * p.F + f] = v;
+            else if constexpr (sizeof(T) == 2) out[r * p.F + f] = f32_to_bf16_rne(v);
+            else out[r * p.F + f] = v;
+            if constexpr (MAXA) p.argmax[r * p.F + f] = p.perm ? p.perm[ps] : static_cast<int64_t>(ps);
+        }
+    }
+    __syncthreads();
+    for (int k = 0; k < kW * per; ++k) {
+        const int64_t r = big_row[k];
+        if (r >= 0) fold_long_row<T, MAXA, kW, 8, OF32>(p, (int64_t)blockIdx.x * kW * per + k, r, sv, sp);
+    }
 }
 
 // Degree class of every row, and their histogram (hist must start at zero).
@@ -833,9 +905,10 @@ int launch_fixup(const SegParams &p, hipStream_t s) {
     if (p.E > 16 * p.chunk * (p.n_rows > 0 ? p.n_rows : 1)) {
         k_segment_fold_groups<T, MAXA, OF32><<<static_cast<unsigned>(p.nchunks), kBlock, 0, s>>>(p);
         PYG_LAUNCH_CHECK();
-        k_segment_fixup<T, MAXA, 16, OF32, true><<<static_cast<unsigned>(p.nchunks), 16 * kWave, 0, s>>>(p);
+        k_segment_fixup_grouped<T, MAXA, 16, OF32><<<static_cast<unsigned>(p.nchunks), 16 * kWave, 0, s>>>(p);
     } else {
-        k_segment_fixup<T, MAXA, 4, OF32, false><<<static_cast<unsigned>(p.nchunks), kBlock, 0, s>>>(p);
+        const int per = fold_per(p.nchunks);
+        k_segment_fixup<T, MAXA, OF32><<<grid_for(p.nchunks, per * (kBlock / kWave), 1 << 26), kBlock, 0, s>>>(p, per);
     }
     PYG_LAUNCH_CHECK();
     return PYG_OK;
