@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from dataclasses import dataclass
 
@@ -165,14 +166,18 @@ def _check(rc: int, what: str):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(device):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    # the raw handle, without a Stream object around it
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 def _need_cuda(name, t, dtype=None, ndim=None):
+    if isinstance(t, torch.Tensor) and t.is_cuda and (dtype is None or t.dtype is dtype) and \
+            (ndim is None or t.dim() == ndim) and t.is_contiguous():
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.device.type != "cuda":
@@ -181,8 +186,7 @@ def _need_cuda(name, t, dtype=None, ndim=None):
         raise ValueError(f"{name} must be {dtype}, got {t.dtype}")
     if ndim is not None and t.dim() != ndim:
         raise ValueError(f"{name} must have {ndim} dims, got shape {tuple(t.shape)}")
-    if not t.is_contiguous():
-        raise ValueError(f"{name} must be contiguous")
+    raise ValueError(f"{name} must be contiguous")
 
 
 def _edge_index(edge_index):
@@ -196,10 +200,16 @@ def _workspace(nbytes: int, device):
     return torch.empty(max(int(nbytes), 1), dtype=torch.uint8, device=device)
 
 
-def _size(fn, *args) -> int:
+@functools.lru_cache(maxsize=1024)
+def _query(name: str, *args) -> int:
     out = ctypes.c_size_t(0)
-    _check(fn(*args, ctypes.byref(out)), fn.__name__)
-    return int(out.value)
+    _check(getattr(library(), name)(*args, ctypes.byref(out)), name)
+    return out.value
+
+
+def _size(fn, *args) -> int:
+    """A workspace query: a function of its integer arguments alone, asked once for each."""
+    return _query(fn.__name__, *args)
 
 
 @dataclass
