@@ -286,9 +286,13 @@ extern "C" int pyg_gcn_propagate(const void *x, int dtype, int64_t N, int64_t F,
     double *dinv = static_cast<double *>(ws);
     float *norm_ws = reinterpret_cast<float *>(static_cast<char *>(ws) + align_up(static_cast<size_t>(N) * sizeof(double), 256));
     void *seg_ws = reinterpret_cast<char *>(norm_ws) + align_up(static_cast<size_t>(E) * 4, 256);
+    // unit weights and few edges: the propagate takes d^-1/2 from the row
+    // lengths itself (a square root per slot, spread over the lanes, against a
+    // launch: a 13k-edge graph 16.4 -> 11.8 us; from 2^20 slots on they outweigh it)
+    const bool lengths = !csr->weight && E <= (int64_t(1) << 20);
     if (csr->weight)
         k_row_dinv_weighted<<<grid_for(N, kBlock / kWave, 1 << 16), kBlock, 0, s>>>(csr->rowptr, csr->weight, N, dinv);
-    else
+    else if (!lengths)
         k_row_dinv_count<<<grid_for(N, kBlock * 4), kBlock, 0, s>>>(csr->rowptr, N, dinv);
     PYG_LAUNCH_CHECK();
     SegmentArgs a{};
@@ -307,8 +311,9 @@ extern "C" int pyg_gcn_propagate(const void *x, int dtype, int64_t N, int64_t F,
     a.sentinel = E;
     a.out = out;
     a.hint = true;
-    a.dinv = dinv;
+    a.dinv = lengths ? nullptr : dinv;
     a.norm_out = norm_out ? norm_out : norm_ws;  // the later feature windows read the weights back
+    a.norms_wanted = norm_out != nullptr;
     return segment_reduce(a, seg_ws, ws_bytes - (static_cast<char *>(seg_ws) - static_cast<char *>(ws)), s);
 }
 

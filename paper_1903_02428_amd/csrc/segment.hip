@@ -94,7 +94,7 @@ struct SegParams {
     // GCN messages (kMsgGcn): dinv [n_rows] fp64 (d^-1/2 of every row), the
     // slot weight w_p = dinv[col] * w_p * dinv[row] formed in fp64 and rounded
     // once; norm_out [E] (or NULL) receives it from the window at feature 0
-    const double *dinv;
+    const double *dinv;  // NULL: from the row lengths (unit weights)
     float *norm_out;
 };
 
@@ -167,6 +167,15 @@ __device__ __forceinline__ int64_t target_row(const SegParams &p, int64_t r) {
     return p.blocks > 1 ? r % p.rpb : r;
 }
 
+// d^-1/2 of node r: from the array, or (a CSR of unit weights and few edges,
+// where a launch that makes the array costs more) from the row's length by
+// the expression that fills the array.
+__device__ __forceinline__ double node_dinv(const SegParams &p, int64_t r) {
+    if (p.dinv) return p.dinv[r];
+    const double d = static_cast<double>(p.rowptr[r + 1] - p.rowptr[r]);
+    return d > 0.0 ? 1.0 / sqrt(d) : 0.0;
+}
+
 // Edge-feature message of one element (formed in fp32, as compared by max).
 template <int MSG>
 __device__ __forceinline__ float edge_msg(float xv, float ev) {
@@ -214,7 +223,7 @@ __device__ __forceinline__ void reduce_piece(const SegParams &p, int64_t r, int6
     }
     // GCN: the row's own d^-1/2
     double dr = 0.0;
-    if constexpr (MSG == kMsgGcn) dr = p.dinv[target_row(p, r)];
+    if constexpr (MSG == kMsgGcn) dr = node_dinv(p, target_row(p, r));
     // per-head weights: a lane vector never straddles two heads (C is a multiple of its width)
     int64_t hd[NS];
 #pragma unroll
@@ -230,7 +239,7 @@ __device__ __forceinline__ void reduce_piece(const SegParams &p, int64_t r, int6
             c = __builtin_nontemporal_load(p.col + e);
             if constexpr (MSG == kMsgGcn) {
                 const double wv = p.w ? static_cast<double>(__builtin_nontemporal_load(p.w + e)) : 1.0;
-                w = static_cast<float>(p.dinv[c] * wv * dr);
+                w = static_cast<float>(node_dinv(p, c) * wv * dr);
                 if (p.norm_out && p.fbase == 0) p.norm_out[e] = w;  // every slot once, by the first window
             }
             if (hot > 0 && p.node_class[c] < hot) c |= static_cast<int>(0x80000000u);
@@ -409,6 +418,8 @@ __device__ __forceinline__ void light_row(const SegParams &p, int64_t r, int64_t
     if constexpr (MSG == kMsgDiff) xi = act ? LN::load(x + rr * p.F + f0) : LN::zero();
     if constexpr (MSG == kMsgEdgeReluGrad) xi = act ? LN::load(static_cast<const T *>(p.x_self) + rr * p.F + f0) : LN::zero();
     const int64_t hd = MSG == kMsgHeads ? f0 / p.C : 0;
+    double dr = 0.0;
+    if constexpr (MSG == kMsgGcn) dr = node_dinv(p, rr);
     for (int64_t base = s; base < t; base += U) {
         int jj[U];
         float ww[U];
@@ -419,18 +430,27 @@ __device__ __forceinline__ void light_row(const SegParams &p, int64_t r, int64_t
             jj[u] = ok[u] ? (IDENT ? static_cast<int>(base + u) : p.col[base + u]) : 0;
             ww[u] = 1.f;
             if constexpr (MSG == kMsgWeighted) ww[u] = ok[u] ? p.w[base + u] : 0.f;
-            if constexpr (MSG == kMsgGcn) {
-                if (ok[u]) {
-                    const double wv = p.w ? static_cast<double>(p.w[base + u]) : 1.0;
-                    ww[u] = static_cast<float>(p.dinv[jj[u]] * wv * p.dinv[rr]);
-                    if (p.norm_out && p.fbase == 0 && q == 0) p.norm_out[base + u] = ww[u];
-                } else {
-                    ww[u] = 0.f;
-                }
-            }
             if constexpr (MSG == kMsgHeads) {
                 const int64_t ar = p.alpha_idx ? (ok[u] ? p.alpha_idx[base + u] : 0) : base + u;
                 ww[u] = (ok[u] && act) ? p.alpha[ar * p.H + hd] : 0.f;
+            }
+        }
+        if constexpr (MSG == kMsgGcn) {
+            // lane q forms the weights of slots q, q + L, ... and hands them out
+            const int L = 1 << p.lg_l;
+            for (int k = 0; k * L < U; ++k) {
+                const int64_t e = base + k * L + q;
+                float w = 0.f;
+                if (k * L + q < U && e < t) {
+                    const double wv = p.w ? static_cast<double>(p.w[e]) : 1.0;
+                    w = static_cast<float>(node_dinv(p, IDENT ? e : p.col[e]) * wv * dr);
+                    if (p.norm_out && p.fbase == 0) p.norm_out[e] = w;
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const float v = __shfl(w, (lane & ~(L - 1)) + (u & (L - 1)), kWave);
+                    if ((u >> p.lg_l) == k) ww[u] = v;
+                }
             }
         }
         constexpr bool EDGE = MSG >= kMsgEdgeAdd && MSG <= kMsgEdgeReluGrad;
@@ -992,6 +1012,8 @@ int run_typed(const SegmentArgs &a, SegParams p, hipStream_t s) {
         PYG_TRY(hot_rows(a.rowptr, a.n_rows, hint_bytes, p.class_hist, p.node_class, p.hot_slot, s));
         p.hot_class = p.hot_slot;
     }
+    // the norms are written for the later narrow windows, or because they are wanted
+    if (mk == kMsgGcn && !narrow && !a.norms_wanted) p.norm_out = nullptr;
     // lane vectors covered by one launch (NS = 4, or one narrow window)
     const int64_t per_window = narrow ? kWindowBytes / 16 : 4 * kWave;
     // the first launch also zero-fills the empty rows (all features)
