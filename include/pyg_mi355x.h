@@ -171,6 +171,14 @@ int pyg_coo_to_csr(const int64_t *edge_index, int64_t E, int64_t N, const float 
                    int64_t *rowptr, int32_t *col, int64_t *perm, float *weight_csr,
                    void *ws, size_t ws_bytes, void *stream);
 
+/* The CSR of the reversed edge list (rows = sources, columns = targets): what
+ * pyg_coo_to_csr gives for [edge_index[1]; edge_index[0]], read from the edge
+ * list as it lies. Arguments, workspace (pyg_coo_to_csr_workspace) and errors
+ * as pyg_coo_to_csr. */
+int pyg_coo_to_csr_reversed(const int64_t *edge_index, int64_t E, int64_t N, const float *edge_weight,
+                            int64_t *rowptr, int32_t *col, int64_t *perm, float *weight_csr,
+                            void *ws, size_t ws_bytes, void *stream);
+
 /* CSR-ordered copy of a COO-ordered edge array: out[p] = in[perm[p]] for
  * p < E, with perm from pyg_coo_to_csr (e.g. fresh edge weights for an
  * existing CSR). in and out are fp32 [E] device arrays and must differ.

@@ -21,7 +21,7 @@ ORDER = {"csr": 0, "coo": 1}
 EXPORTED = [
     "pyg_strerror", "pyg_abi_version", "pyg_degree_workspace", "pyg_degree", "pyg_degree_csr",
     "pyg_coo_to_csr_workspace",
-    "pyg_coo_to_csr", "pyg_gather_edges",
+    "pyg_coo_to_csr", "pyg_coo_to_csr_reversed", "pyg_gather_edges",
     "pyg_gcn_norm_workspace", "pyg_gcn_norm", "pyg_gcn_norm_csr_workspace", "pyg_gcn_norm_csr",
     "pyg_propagate_workspace", "pyg_propagate", "pyg_propagate_edge", "pyg_propagate_edge_encoded_workspace",
     "pyg_propagate_edge_encoded", "pyg_propagate_backward_workspace",
@@ -85,6 +85,7 @@ def library() -> ctypes.CDLL:
             "pyg_degree_csr": [ctypes.POINTER(_Csr), p, p],
             "pyg_coo_to_csr_workspace": [i64, i64, sz],
             "pyg_coo_to_csr": [p, i64, i64, p, p, p, p, p, p, ctypes.c_size_t, p],
+            "pyg_coo_to_csr_reversed": [p, i64, i64, p, p, p, p, p, p, ctypes.c_size_t, p],
             "pyg_gather_edges": [p, i64, p, p, p],
             "pyg_gcn_norm_workspace": [i64, i64, sz],
             "pyg_gcn_norm": [p, p, i64, i64, p, p, p, ctypes.c_size_t, p],
@@ -348,6 +349,10 @@ def coo_to_csr(edge_index: torch.Tensor, num_nodes: int, edge_weight: torch.Tens
                chunk: int = 0, out: CSR | None = None, workspace: torch.Tensor | None = None) -> CSR:
     """Build the CSR; `out` (a CSR of the same shape) and `workspace` may be
     passed to reuse device buffers."""
+    return _build_csr("pyg_coo_to_csr", edge_index, num_nodes, edge_weight, chunk, out, workspace)
+
+
+def _build_csr(entry: str, edge_index, num_nodes, edge_weight=None, chunk=0, out=None, workspace=None) -> CSR:
     lib = library()
     E = _edge_index(edge_index)
     dev = edge_index.device
@@ -366,8 +371,8 @@ def coo_to_csr(edge_index: torch.Tensor, num_nodes: int, edge_weight: torch.Tens
         wcsr = torch.empty(E, dtype=torch.float32, device=dev) if edge_weight is not None else None
     nbytes = _size(lib.pyg_coo_to_csr_workspace, E, num_nodes)
     ws = workspace if workspace is not None and workspace.numel() >= nbytes else _workspace(nbytes, dev)
-    _check(lib.pyg_coo_to_csr(_ptr(edge_index), E, num_nodes, _ptr(edge_weight), _ptr(rowptr), _ptr(col),
-                              _ptr(perm), _ptr(wcsr), _ptr(ws), nbytes, _stream(dev)), "pyg_coo_to_csr")
+    _check(getattr(lib, entry)(_ptr(edge_index), E, num_nodes, _ptr(edge_weight), _ptr(rowptr), _ptr(col),
+                               _ptr(perm), _ptr(wcsr), _ptr(ws), nbytes, _stream(dev)), entry)
     if out is not None:
         out.chunk = chunk
         return out
@@ -1073,7 +1078,7 @@ class Graph:
         self.N = num_nodes
         self.edge_weight = edge_weight
         self.csr = coo_to_csr(edge_index, num_nodes, edge_weight)
-        self.csr_t = coo_to_csr(reverse_edges(edge_index), num_nodes, edge_weight)
+        self.csr_t = _build_csr("pyg_coo_to_csr_reversed", edge_index, num_nodes, edge_weight)
         self._map_t = None
 
     @property

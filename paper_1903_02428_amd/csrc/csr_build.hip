@@ -1024,7 +1024,7 @@ namespace {
 // The stable sort of the edges by sort key (target, or source block then
 // target), carrying edge id, source and weight; rowptr over the B * N rows
 // from the key changes of the sorted keys.
-int coo_to_csr_impl(const int64_t *edge_index, int64_t E, int64_t N, int64_t B, const float *edge_weight,
+int coo_to_csr_impl(const int64_t *src, const int64_t *dst, int64_t E, int64_t N, int64_t B, const float *edge_weight,
                     int64_t *rowptr, int32_t *col, int64_t *perm, float *weight_csr, void *ws, size_t ws_bytes,
                     hipStream_t s) {
     if (!edge_weight) weight_csr = nullptr;
@@ -1032,8 +1032,6 @@ int coo_to_csr_impl(const int64_t *edge_index, int64_t E, int64_t N, int64_t B, 
     if (ws_bytes < w.bytes || (w.bytes > 256 && !ws)) return PYG_ERR_WORKSPACE;
     const int64_t rows = B * N;
     if (E == 0) return fill<int64_t>(rowptr, rows + 1, 0, s);
-    const int64_t *src = edge_index;
-    const int64_t *dst = edge_index + E;
     // few edges: the passes below are eight launches of latency
     if (B == 1 && small_csr_ok(E, N))
         return small_csr(src, dst, E, N, weight_csr ? edge_weight : nullptr, rowptr, col, perm, weight_csr, s);
@@ -1132,7 +1130,17 @@ extern "C" int pyg_coo_to_csr(const int64_t *edge_index, int64_t E, int64_t N, c
     if (E < 0 || N < 0 || !rowptr) return PYG_ERR_INVALID_ARG;
     if (E > 0 && (!edge_index || !col || !perm || N == 0)) return PYG_ERR_INVALID_ARG;
     if (N >= (int64_t(1) << 31) || E >= (int64_t(1) << 31)) return PYG_ERR_UNSUPPORTED;
-    return coo_to_csr_impl(edge_index, E, N, 1, edge_weight, rowptr, col, perm, weight_csr, ws, ws_bytes,
+    return coo_to_csr_impl(edge_index, edge_index + E, E, N, 1, edge_weight, rowptr, col, perm, weight_csr, ws, ws_bytes,
+                           static_cast<hipStream_t>(stream));
+}
+
+extern "C" int pyg_coo_to_csr_reversed(const int64_t *edge_index, int64_t E, int64_t N, const float *edge_weight,
+                                       int64_t *rowptr, int32_t *col, int64_t *perm, float *weight_csr, void *ws,
+                                       size_t ws_bytes, void *stream) {
+    if (E < 0 || N < 0 || !rowptr) return PYG_ERR_INVALID_ARG;
+    if (E > 0 && (!edge_index || !col || !perm || N == 0)) return PYG_ERR_INVALID_ARG;
+    if (N >= (int64_t(1) << 31) || E >= (int64_t(1) << 31)) return PYG_ERR_UNSUPPORTED;
+    return coo_to_csr_impl(edge_index + E, edge_index, E, N, 1, edge_weight, rowptr, col, perm, weight_csr, ws, ws_bytes,
                            static_cast<hipStream_t>(stream));
 }
 
@@ -1149,7 +1157,7 @@ extern "C" int pyg_coo_to_csr_blocked(const int64_t *edge_index, int64_t E, int6
     if (E < 0 || N < 0 || !rowptr || B < 2 || B > 32) return PYG_ERR_INVALID_ARG;
     if (E > 0 && (!edge_index || !col || N == 0)) return PYG_ERR_INVALID_ARG;
     if (N >= (int64_t(1) << 31) || E >= (int64_t(1) << 31) || B * N >= (int64_t(1) << 31)) return PYG_ERR_UNSUPPORTED;
-    return coo_to_csr_impl(edge_index, E, N, B, edge_weight, rowptr, col, perm, weight_csr, ws, ws_bytes,
+    return coo_to_csr_impl(edge_index, edge_index + E, E, N, B, edge_weight, rowptr, col, perm, weight_csr, ws, ws_bytes,
                            static_cast<hipStream_t>(stream));
 }
 

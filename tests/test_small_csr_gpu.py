@@ -37,3 +37,18 @@ def test_small_csr_bits(case, kind):
         assert np.array_equal(c.perm.cpu().numpy(), perm)
         assert np.array_equal(c.col.cpu().numpy(), col)
     assert np.array_equal(csr.weight.cpu().numpy(), w[perm])
+
+
+@pytest.mark.parametrize("case", [(700, 24575), (30000, 90000), (70000, 1_500_001)])
+def test_reversed_csr_bits(case):
+    """The CSR of the reversed edge list read in place (as Graph builds it):
+    both build routes, with and without weights, against the swapped list's."""
+    import paper_1903_02428_amd as pyg
+    N, E = case
+    rng = np.random.default_rng(7100 + E)
+    ei = to_dev(synth.random_coo(rng, N, E))
+    for w in (None, to_dev(rng.standard_normal(E).astype(np.float32))):
+        got = pyg.Graph(ei, N, w).csr_t
+        ref = pyg.coo_to_csr(pyg.reverse_edges(ei), N, w)
+        for a, b in zip((got.rowptr, got.col, got.perm, got.weight), (ref.rowptr, ref.col, ref.perm, ref.weight)):
+            assert (a is None and b is None) or torch.equal(a, b)
