@@ -215,6 +215,23 @@ constexpr int kSegMsgEdgeReluGrad = 100;
 // formed in fp64 and rounded once (w = csr weight, or 1), optionally written out.
 constexpr int kSegMsgGcn = 101;
 int64_t segment_chunk(int64_t E, int64_t n_rows, int64_t requested);
+// Mean row length up to which rows go to sub-groups ("light" rows) instead of
+// whole wavefronts: kNN rows of 16 slots gain 25 % that way.
+#ifndef PYG_LIGHT_MAX_DEGREE
+#define PYG_LIGHT_MAX_DEGREE 16
+#endif
+constexpr int64_t kLightMaxDegree = PYG_LIGHT_MAX_DEGREE;
+// Among light rows, one of more slots than this is left to the whole
+// wavefront: a sub-group would walk it alone while the others wait. Twice the
+// mean, 16 to 32 (power law, 1.6M edges of mean 8: the edge-message kernel
+// 298 us without the limit, 191 at 32, 157 at 16; uniform rows of mean 16: 79 us
+// without, 85 at 32, 111 at 16, which half of them exceed).
+// At most the chunk: longer rows are cut into pieces.
+static inline int64_t light_row_slots(int64_t E, int64_t n_rows, int64_t chunk) {
+    int64_t m = n_rows > 0 ? 2 * E / n_rows : 0;
+    m = m < 16 ? 16 : m > 32 ? 32 : m;
+    return m < chunk ? m : chunk;
+}
 
 // Chunks one wavefront of a fold launch looks at: enough wavefronts first.
 constexpr int kFoldPerMax = 16;

@@ -240,8 +240,7 @@ template <typename TG, typename T, int KIND>
 int launch_fused(const FusedParams &p, hipStream_t s) {
     constexpr int U = KIND == kWeight ? 4 : 2;  // slots in flight per lane: registers, and with them wavefronts, count for more
     const unsigned grid = static_cast<unsigned>((p.zero_items + p.walk.nchunks + 3) / 4);
-    // rows of at most 16 slots on average go to sub-groups, as in the segment kernel
-    if (p.lg < 6 && p.walk.E <= 16 * p.walk.N)
+    if (p.lg < 6 && p.walk.E <= kLightMaxDegree * p.walk.N)
         k_fused_backward<TG, T, KIND, U, true><<<grid, kBlock, 0, s>>>(p);
     else
         k_fused_backward<TG, T, KIND, U, false><<<grid, kBlock, 0, s>>>(p);
@@ -281,7 +280,7 @@ int fused_backward(const FusedBackwardArgs &a, void *ws, size_t ws_bytes, hipStr
     const FusedWs w = carve_fused(ws, a.N, a.F, a.E, chunk);
     if (!ws || ws_bytes < w.bytes) return PYG_ERR_WORKSPACE;
     FusedParams p{};
-    p.walk = {a.rowptr, a.N, a.E, chunk, (a.E + chunk - 1) / chunk, w.head_row};
+    p.walk = {a.rowptr, a.N, a.E, chunk, light_row_slots(a.E, a.N, chunk), (a.E + chunk - 1) / chunk, w.head_row};
     int64_t per = ((a.N + 1023) / 1024 + kWave - 1) / kWave * kWave;
     p.zero_rows = per > kWave ? per : kWave;
     p.zero_items = (a.N + p.zero_rows - 1) / p.zero_rows;

@@ -571,7 +571,7 @@ void set_windows(GatParams &p, int64_t sz, int64_t C, int max_lanes) {
 }
 
 void set_walk(GatParams &p, const pyg_csr *csr, int64_t chunk, int32_t *head_row) {
-    p.walk = {csr->rowptr, csr->N, csr->E, chunk, (csr->E + chunk - 1) / chunk, head_row};
+    p.walk = {csr->rowptr, csr->N, csr->E, chunk, light_row_slots(csr->E, csr->N, chunk), (csr->E + chunk - 1) / chunk, head_row};
     int64_t per = (csr->N + 1023) / 1024;
     per = (per + kWave - 1) / kWave * kWave;
     p.zero_rows = per > kWave ? per : kWave;
@@ -589,15 +589,12 @@ int set_hint(GatParams &p, const GatWs &w, int64_t sz, hipStream_t s) {
     return PYG_OK;
 }
 
-// mean row length up to which rows go to sub-groups, as in the segment kernel
-constexpr int64_t kLight = 16;
-
 template <typename T, bool GRAD>
 int launch_forward(const GatParams &p, hipStream_t s) {
     constexpr int U = 4;
     const int64_t items = p.zero_items + p.walk.nchunks * p.nwin;
     const unsigned grid = static_cast<unsigned>((items + 3) / 4);
-    const bool light = p.lg < 6 && p.walk.E <= kLight * p.walk.N;
+    const bool light = p.lg < 6 && p.walk.E <= kLightMaxDegree * p.walk.N;
     if (light) k_gat_forward<T, U, GRAD, true><<<grid, kBlock, 0, s>>>(p);
     else k_gat_forward<T, U, GRAD, false><<<grid, kBlock, 0, s>>>(p);
     PYG_LAUNCH_CHECK();
@@ -619,7 +616,7 @@ int launch_backward(const GatParams &p, const float *all, const float *plus, con
     PYG_LAUNCH_CHECK();
     const int64_t items = p.zero_items + p.walk.nchunks * p.nwin;
     const unsigned grid = static_cast<unsigned>((items + 3) / 4);
-    const bool light = p.lg < 6 && p.walk.E <= kLight * p.walk.N;
+    const bool light = p.lg < 6 && p.walk.E <= kLightMaxDegree * p.walk.N;
     if (light) k_gat_backward<T, U, true><<<grid, kBlock, 0, s>>>(p);
     else k_gat_backward<T, U, false><<<grid, kBlock, 0, s>>>(p);
     PYG_LAUNCH_CHECK();

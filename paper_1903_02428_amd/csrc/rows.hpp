@@ -43,6 +43,7 @@ struct RowWalk {
     int64_t N;  // rows
     int64_t E;
     int64_t chunk;
+    int64_t light_row;  // light rows: slots up to which a sub-group takes a row
     int64_t nchunks;
     int32_t *head_row;  // [nchunks]: the long row that starts in the chunk, or -1
 };
@@ -105,18 +106,20 @@ __device__ __forceinline__ void walk_heavy(const RowWalk &p, int64_t c, int lane
     p.head_row[c] = head;  // uniform: every lane stores the same value
 }
 
-// Light rows: each of the 64 >> lg sub-groups takes a row of its own,
-// op.light(r, s, t, mine); pieces of long rows go to the whole wavefront.
+// Light rows: each of the 64 >> lg sub-groups takes a row of its own of up to
+// light_row slots, op.light(r, s, t, mine); longer rows and pieces of long
+// ones go to the whole wavefront (op.run).
 template <class OP>
 __device__ __forceinline__ void walk_light(const RowWalk &p, int64_t c, int lane, int lg, OP &op) {
     const int64_t e0 = c * p.chunk;
     const int64_t e1 = (e0 + p.chunk) < p.E ? (e0 + p.chunk) : p.E;
     const int64_t rA = uniform64(wave_lower_bound(p.rowptr, p.N + 1, e0, lane));
     const int64_t rpA = uniform64(p.rowptr[rA]);
+    bool cont = rA > 0 && rpA > e0 && rpA - uniform64(p.rowptr[rA - 1]) > p.chunk;
     const int S = kWave >> lg, sg = lane >> lg;
     int32_t head = -1;
     int64_t rb = rA;
-    while (rb < p.N) {
+    while (true) {
         const int64_t rp = p.rowptr[(rb + lane) < p.N ? (rb + lane) : p.N];
         // rows rb .. rb + cnt - 1 start in the chunk; lane i + 1 holds the end of row rb + i
         const bool in = lane < kWave - 1 && rb + lane < p.N && rp < e1;
@@ -130,26 +133,34 @@ __device__ __forceinline__ void walk_light(const RowWalk &p, int64_t c, int lane
             const int i = i0 + sg;
             const int ii = i < cnt ? i : cnt - 1;
             const int64_t s = __shfl(rp, ii, kWave), t = __shfl(rp, ii + 1, kWave);
-            const bool is_long = i < cnt && t - s > p.chunk;  // only the chunk's last row can be long
-            const uint64_t lm = __ballot(is_long);
-            if (lm) head = static_cast<int32_t>(rb + i0 + ((__ffsll(static_cast<unsigned long long>(lm)) - 1) >> lg));
-            op.light(rb + i, s, t, i < cnt && !is_long && t > s);
+            op.light(rb + i, s, t, i < cnt && t > s && t - s <= p.light_row);
+        }
+        // the whole wavefront's: rows above light_row slots, the first piece of
+        // a long row (only the chunk's last row can be one), the piece that came in
+        const int64_t len = __shfl_down(rp, 1, kWave) - rp;
+        uint64_t jobs = __ballot(lane < cnt && len > p.light_row);
+        while (cont || jobs) {
+            int64_t r = rA - 1, s = e0, t = rpA < e1 ? rpA : e1, slot = 2 * c;
+            int kind = kRowPiece;
+            if (!cont) {
+                const int k = __ffsll(static_cast<unsigned long long>(jobs)) - 1;
+                jobs &= jobs - 1;
+                r = rb + k;
+                s = lane_value64(rp, k);
+                t = lane_value64(rp, k + 1);
+                kind = kRowFull;
+                if (t - s > p.chunk) {
+                    kind = kRowPiece;
+                    slot = 2 * c + 1;
+                    t = e1;
+                    head = static_cast<int32_t>(r);
+                }
+            }
+            cont = false;
+            op.run(r, s, t, kind, slot);
         }
         if (cnt < kWave - 1) break;  // the chunk's rows end in this batch
         rb += cnt;
-    }
-    head = __builtin_amdgcn_readfirstlane(head);
-    // pieces: the long row that started earlier, and the one that starts here
-    for (int k = 0; k < 2; ++k) {
-        int64_t r, s, t, slot = 2 * c + k;
-        if (k == 0) {
-            if (!(rA > 0 && rpA > e0) || rpA - uniform64(p.rowptr[rA - 1]) <= p.chunk) continue;
-            r = rA - 1, s = e0, t = rpA < e1 ? rpA : e1;
-        } else {
-            if (head < 0) continue;
-            r = head, s = uniform64(p.rowptr[head]), t = e1;
-        }
-        op.run(r, s, t, kRowPiece, slot);
     }
     p.head_row[c] = head;
 }

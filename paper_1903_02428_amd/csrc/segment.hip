@@ -69,6 +69,7 @@ struct SegParams {
     int64_t n_rows;
     int64_t E;
     int64_t chunk;
+    int64_t light_row;  // light rows: slots up to which a sub-group takes a row
     int64_t nchunks;
     int lg_l;  // log2 of lanes per feature row
     int mean;
@@ -101,10 +102,6 @@ struct SegParams {
 // Measured on the large power-law graph (F = 128): fp32 rows (512 B) gain
 // 10 % with a 8-12 MB hot budget; bf16 rows (256 B) lose at every budget, so
 // the hint is used for rows of at least 512 B only.
-#ifndef PYG_LIGHT_MAX_DEGREE
-#define PYG_LIGHT_MAX_DEGREE 16  // kNN rows of 16 slots gain 25 % as light rows
-#endif
-constexpr int64_t kLightMaxDegree = PYG_LIGHT_MAX_DEGREE;  // mean row length up to which rows go to sub-groups
 constexpr int64_t kHotBudgetBytes = 12ll << 20;  // hot rows kept cacheable
 // Narrow windows: when the source rows are large in total and wider than one
 // cache line, the row is reduced one 128-byte window (32 fp32 / 64 bf16
@@ -547,8 +544,18 @@ __device__ __forceinline__ void zero_empty_rows(const SegParams &p, int64_t z, i
     }
 }
 
+// Rows of a launch: whole wavefronts take rows (kHeavy), or sub-groups do
+// (light rows): all but the long ones (kLightShort), or those of up to
+// light_row slots with the rest left to the whole wavefront (kLightMixed). The
+// mixed form pays where chunks are large enough for a sub-group to be stuck
+// in a row while the others wait: from 64 slots on (graphs from 262,144 edges;
+// power law, 2.4M edges 352 -> 237 us). Below, its bookkeeping costs more than
+// it saves (mini-batch of 2,048 graphs, 32-slot chunks: 15.6 us short, 19.9 mixed).
+constexpr int kHeavy = 0, kLightShort = 1, kLightMixed = 2;
+inline bool mixed_rows(const SegParams &p) { return p.chunk >= 64; }
+
 // One wavefront's work on chunk c (features p.fbase .. p.fbase + p.fcnt).
-template <typename T, bool VEC, int NS, int U, int MSG, bool MAXA, bool IDENT, bool LIGHT, bool OF32>
+template <typename T, bool VEC, int NS, int U, int MSG, bool MAXA, bool IDENT, int LIGHT, bool OF32>
 __device__ __forceinline__ void segment_chunk_work(const SegParams &p, int64_t c, int lane) {
     const int64_t e0 = c * p.chunk;
     const int64_t e1 = (e0 + p.chunk) < p.E ? (e0 + p.chunk) : p.E;
@@ -558,15 +565,66 @@ __device__ __forceinline__ void segment_chunk_work(const SegParams &p, int64_t c
     const int hot = (!IDENT && p.hot_class) ? __builtin_amdgcn_readfirstlane(*p.hot_class) : 0;
     int32_t head = -1;
 
-    // a long row that started in an earlier chunk: reduce its piece here
-    if (rA > 0 && rpA > e0) {
-        const int64_t s0 = uniform64(p.rowptr[rA - 1]);
-        if (rpA - s0 > p.chunk)
-            reduce_piece<T, VEC, NS, U, MSG, MAXA, IDENT, OF32>(p, rA - 1, e0, rpA < e1 ? rpA : e1, kPartial, 2 * c, lane, hot);
-    }
+    // a long row that started in an earlier chunk has a piece here
+    bool cont = rA > 0 && rpA > e0 && rpA - uniform64(p.rowptr[rA - 1]) > p.chunk;
     // rows whose first slot lies in [e0, e1) (the last chunk also takes the
     // empty rows that start at E)
-    if constexpr (LIGHT) {
+    if constexpr (LIGHT == kLightMixed) {
+        const int S = kWave >> p.lg_l;
+        const int sg = lane >> p.lg_l;
+        int64_t rb = rA;
+        while (true) {
+            const int64_t rp = p.rowptr[(rb + lane) < p.n_rows ? (rb + lane) : p.n_rows];
+            // rows rb .. rb+cnt-1 start in the chunk (rows starting at E are
+            // empty: zero-filled separately); lane i+1 holds the end of row rb+i
+            const bool in = lane < kWave - 1 && rb + lane < p.n_rows && rp < (last ? p.E : e1);
+            const int cnt = __popcll(__ballot(in));
+            const int64_t s_first = lane_value64(rp, 0);
+            if (cnt == kWave - 1 && lane_value64(rp, kWave - 1) == s_first) {
+                // 63 empty rows in a row: skip to the last row that starts at s_first
+                rb = uniform_lower_bound(p.rowptr, p.n_rows + 1, s_first + 1) - 1;
+                continue;
+            }
+            for (int i0 = 0; i0 < cnt; i0 += S) {
+                const int i = i0 + sg;
+                const int ii = i < cnt ? i : cnt - 1;
+                const int64_t s = __shfl(rp, ii, kWave), t = __shfl(rp, ii + 1, kWave);
+                light_row<T, VEC, U, MSG, MAXA, IDENT, OF32>(p, rb + i, s, t, i < cnt && t > s && t - s <= p.light_row, lane);
+            }
+            // the whole wavefront: rows above light_row slots (a sub-group would
+            // walk one alone while the others wait), the first piece of a long
+            // row (only the chunk's last row can be one), the piece that came in
+            const int64_t len = __shfl_down(rp, 1, kWave) - rp;
+            uint64_t jobs = __ballot(lane < cnt && len > p.light_row);
+            while (cont || jobs) {
+                int64_t r = rA - 1, s = e0, t = rpA < e1 ? rpA : e1, slot = 2 * c;
+                int kind = kPartial;
+                if (!cont) {
+                    const int k = __ffsll(static_cast<unsigned long long>(jobs)) - 1;
+                    jobs &= jobs - 1;
+                    r = rb + k;
+                    s = lane_value64(rp, k);
+                    t = lane_value64(rp, k + 1);
+                    kind = kFull;
+                    if (t - s > p.chunk) {
+                        kind = kPartial;
+                        slot = 2 * c + 1;
+                        t = e1;
+                        head = static_cast<int32_t>(r);
+                    }
+                }
+                cont = false;
+                reduce_piece<T, VEC, NS, U, MSG, MAXA, IDENT, OF32>(p, r, s, t, kind, slot, lane, 0);
+            }
+            if (cnt < kWave - 1) break;  // the chunk's rows end in this batch
+            rb += cnt;
+        }
+        p.head_row[c] = head;  // uniform: every lane stores the same value (no lane-0 branch)
+        return;
+    }
+    if (cont)
+        reduce_piece<T, VEC, NS, U, MSG, MAXA, IDENT, OF32>(p, rA - 1, e0, rpA < e1 ? rpA : e1, kPartial, 2 * c, lane, hot);
+    if constexpr (LIGHT == kLightShort) {
         const int S = kWave >> p.lg_l;
         const int sg = lane >> p.lg_l;
         int64_t rb = rA;
@@ -631,7 +689,7 @@ __device__ __forceinline__ void segment_chunk_work(const SegParams &p, int64_t c
     p.head_row[c] = head;  // uniform: every lane stores the same value (no lane-0 branch)
 }
 
-template <typename T, bool VEC, int NS, int U, int MSG, bool MAXA, bool IDENT, bool LIGHT, bool OF32 = false>
+template <typename T, bool VEC, int NS, int U, int MSG, bool MAXA, bool IDENT, int LIGHT, bool OF32 = false>
 __global__ __launch_bounds__(kBlock) void k_segment(SegParams p) {
     const int lane = threadIdx.x & (kWave - 1);
     int64_t c = uniform64((int64_t)blockIdx.x * (kBlock / kWave) + (threadIdx.x / kWave));
@@ -940,10 +998,11 @@ int launch_window(const SegParams &p, bool light, bool fixup, hipStream_t s) {
     const int64_t nc = p.nchunks * (p.nwin > 1 ? p.nwin : 1) + p.zero_items;
     const unsigned grid = static_cast<unsigned>((nc + (kBlock / kWave) - 1) / (kBlock / kWave));
     if constexpr (NS == 1) {
-        if (light) k_segment<T, VEC, NS, U, MSG, MAXA, IDENT, true><<<grid, kBlock, 0, s>>>(p);
-        else k_segment<T, VEC, NS, U, MSG, MAXA, IDENT, false><<<grid, kBlock, 0, s>>>(p);
+        if (light && mixed_rows(p)) k_segment<T, VEC, NS, U, MSG, MAXA, IDENT, kLightMixed><<<grid, kBlock, 0, s>>>(p);
+        else if (light) k_segment<T, VEC, NS, U, MSG, MAXA, IDENT, kLightShort><<<grid, kBlock, 0, s>>>(p);
+        else k_segment<T, VEC, NS, U, MSG, MAXA, IDENT, kHeavy><<<grid, kBlock, 0, s>>>(p);
     } else {
-        k_segment<T, VEC, NS, U, MSG, MAXA, IDENT, false><<<grid, kBlock, 0, s>>>(p);
+        k_segment<T, VEC, NS, U, MSG, MAXA, IDENT, kHeavy><<<grid, kBlock, 0, s>>>(p);
     }
     PYG_LAUNCH_CHECK();
     return fixup ? launch_fixup<T, MAXA>(p, s) : PYG_OK;
@@ -1206,8 +1265,9 @@ int launch_blocked(const SegParams &p, bool light, hipStream_t s) {
     constexpr int U = 8;  // gathers in flight per lane, as in the unblocked kernel
     const int64_t nc = p.nchunks * (p.nwin > 1 ? p.nwin : 1) + p.zero_items;
     const unsigned grid = static_cast<unsigned>((nc + (kBlock / kWave) - 1) / (kBlock / kWave));
-    if (light) k_segment<T, true, 1, U, MSG, MAXA, false, true, true><<<grid, kBlock, 0, s>>>(p);
-    else k_segment<T, true, 1, U, MSG, MAXA, false, false, true><<<grid, kBlock, 0, s>>>(p);
+    if (light && mixed_rows(p)) k_segment<T, true, 1, U, MSG, MAXA, false, kLightMixed, true><<<grid, kBlock, 0, s>>>(p);
+    else if (light) k_segment<T, true, 1, U, MSG, MAXA, false, kLightShort, true><<<grid, kBlock, 0, s>>>(p);
+    else k_segment<T, true, 1, U, MSG, MAXA, false, kHeavy, true><<<grid, kBlock, 0, s>>>(p);
     PYG_LAUNCH_CHECK();
     return PYG_OK;
 }
@@ -1332,6 +1392,7 @@ int segment_reduce_blocked(const SegmentArgs &a, int64_t B, void *ws, size_t ws_
     p.n_rows = B * N;
     p.E = E;
     p.chunk = chunk;
+    p.light_row = light_row_slots(E, B * N, chunk);
     p.nchunks = (E + chunk - 1) / chunk;
     p.mean = 0;  // partial sums; the fold divides
     p.sentinel = E;
@@ -1490,6 +1551,7 @@ int segment_reduce(const SegmentArgs &a, void *ws, size_t ws_bytes, hipStream_t 
     p.n_rows = a.n_rows;
     p.E = a.E;
     p.chunk = chunk;
+    p.light_row = light_row_slots(a.E, a.n_rows, chunk);
     p.nchunks = a.E > 0 ? (a.E + chunk - 1) / chunk : 0;
     p.mean = a.aggr == PYG_MEAN;
     p.sentinel = a.sentinel;
