@@ -1177,8 +1177,15 @@ def _gat_backward(grad_out, x, a_src, kept, csr_t: CSR, slope: float):
     lib = library()
     _need_cuda("grad_out", grad_out, x.dtype, 2)
     (N, F), H, dev = x.shape, a_src.shape[1], x.device
-    if grad_out.shape != x.shape:
-        raise ValueError("grad_out must match x")
+    # what autograd kept comes back through a program's own hooks, if it has any
+    _need_cuda("x", x, None, 2)
+    _need_cuda("a_src", a_src, torch.float32, 2)
+    for name, t, shape in zip(("P", "P+", "the row state"), kept, ((N, F), (N, F), (N, H, 4))):
+        _need_cuda(name, t, torch.float32)
+        if t.shape != shape:
+            raise ValueError(f"{name} must be {shape}, got {tuple(t.shape)}")
+    if grad_out.shape != x.shape or csr_t.N != N or a_src.shape[0] != N:
+        raise ValueError("grad_out, a_src and csr_t must match x")
     gx, gs, gd = torch.empty_like(x), torch.empty_like(a_src), torch.empty_like(a_src)
     nbytes = _size(lib.pyg_gat_backward_workspace, N, H, F // H, csr_t.E, csr_t.chunk)
     ws = _workspace(nbytes, dev)
@@ -1222,7 +1229,8 @@ class GATAttention(torch.autograd.Function):
         H = a_src.shape[1]
         if kept:
             gout, xc = grad_out.contiguous().to(x.dtype), x.detach().contiguous()
-            gout, xc = (t if _aligned16(t) else t.clone() for t in (gout, xc))
+            gout, xc, *kept = (t if t.is_contiguous() and _aligned16(t) else
+                               t.clone(memory_format=torch.contiguous_format) for t in (gout, xc, *kept))
             grads = _gat_backward(gout, xc, a_src.detach().contiguous(), kept, g.csr_t, ctx.slope)
             return tuple(v if need else None for v, need in zip(grads, ctx.needs_input_grad)) + (None, None)
         need_logits = ctx.needs_input_grad[1] or ctx.needs_input_grad[2]

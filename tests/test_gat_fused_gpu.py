@@ -170,3 +170,36 @@ def test_gat_fused_takes_what_the_separate_kernels_took(pyg):
         res.append((out.detach(), gx))
     for p, q in zip(*res):
         assert torch.allclose(p, q, rtol=1e-5, atol=1e-5)
+
+
+def test_gat_fused_saved_tensor_hooks(pyg):
+    # what hooks hand back to the gradient: host copies brought back, unaligned
+    # and transposed copies (the same bits), and tensors that no kernel may read
+    rng = np.random.default_rng(5400)
+    N, H, C = 50, 2, 8
+    graph = pyg.Graph(to_dev(synth.random_coo(rng, N, 400)), N)
+    x, g = (to_dev(rng.standard_normal((N, H * C)).astype(np.float32)) for _ in range(2))
+    logits = [to_dev(rng.standard_normal((N, H)).astype(np.float32)) for _ in range(2)]
+
+    def grads(hooks):
+        dev = [t.detach().clone().requires_grad_(True) for t in (x, *logits)]
+        with hooks:
+            out = pyg.GATAttention.apply(*dev, graph, 0.2)
+        return torch.autograd.grad(out, dev, g)
+
+    def unaligned(t):
+        buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+        return buf[1:].view(t.shape).copy_(t)
+
+    def strided(t):
+        return t.transpose(0, 1).contiguous().transpose(0, 1)
+
+    hook = torch.autograd.graph.saved_tensors_hooks
+    ref = grads(hook(lambda t: t, lambda t: t))
+    for h in (torch.autograd.graph.save_on_cpu(), hook(lambda t: t, unaligned), hook(lambda t: t, strided)):
+        for p, q in zip(ref, grads(h)):
+            assert torch.equal(p, q)
+    # refused on the host, before any launch: another device, another type
+    for bad in (lambda t: t.cpu(), lambda t: t.double()):
+        with pytest.raises((ValueError, RuntimeError)):
+            grads(hook(lambda t: t, lambda t, bad=bad: bad(t) if t.dim() == 3 else t))
