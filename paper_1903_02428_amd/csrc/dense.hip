@@ -238,6 +238,11 @@ __global__ __launch_bounds__(kBlock) void k_dense(const uint16_t *__restrict__ x
 #define PYG_DENSE_F32_PERSIST 2
 #endif
 
+__global__ void k_theta_copy(const float *__restrict__ theta, int64_t n, float *__restrict__ copy) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        copy[i] = theta[i];
+}
+
 __global__ void k_theta_t_f32(const float *__restrict__ theta, int64_t Fi, int64_t Fo, int64_t Kp, int64_t Fo_pad,
                               float *__restrict__ tt) {
     const int64_t n = Fo_pad * Kp;
@@ -477,6 +482,15 @@ extern "C" int pyg_dense_transform(const void *x, int x_dtype, int64_t N, int64_
         const bool vec = Fi % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0;
         const float *xf = static_cast<const float *>(x), *th = static_cast<const float *>(theta);
         const int64_t nblocks = (N + kRowsWave * (kBlock / kWave) - 1) / (kRowsWave * (kBlock / kWave));
+        // out over Theta's memory: the product reads a copy (ws holds Fi * Fo floats)
+        const char *tb = static_cast<const char *>(theta);
+        if (ob < tb + Fi * Fo * xsz && tb < ob + N * Fo * osz) {
+            float *copy = static_cast<float *>(ws);
+            k_theta_copy<<<grid_for(Fi * Fo, kBlock * 4), kBlock, 0, s>>>(th, Fi * Fo, copy);
+            PYG_LAUNCH_CHECK();
+            return out_dtype == PYG_F32 ? dense_f32(xf, N, Fi, copy, Fo, static_cast<float *>(out), vec, s)
+                                        : dense_f32(xf, N, Fi, copy, Fo, static_cast<uint16_t *>(out), vec, s);
+        }
         // persistent workgroups with the whole Theta^T staged once: K of one
         // stage, columns for its 128-column tiles and two rounds of row blocks
         if (Fi <= 128 && Fo > 64 && nblocks >= PYG_DENSE_F32_PERSIST * kPersistBlocksF) {

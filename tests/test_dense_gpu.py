@@ -138,3 +138,18 @@ def test_gcn_layer_chain(pyg):
     g = outb.float().cpu().numpy().astype(np.float64)
     bound = 1e-2 * np.abs(refb) + (2.0 ** -7 + 1e-5) * sabsb + 1e-6
     assert np.all(np.abs(g - refb) <= bound), f"gcn layer chain (bf16): worst {np.max(np.abs(g - refb) / bound)}"
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("shape", [(300, 300, 37), (96, 96, 96), (600, 150, 16)])
+def test_dense_transform_out_over_theta(pyg, dtype, shape):
+    # a result written over Theta's own memory: the same bits as beside it
+    N, Fi, Fo = shape
+    rng = np.random.default_rng(11)
+    x, t = (to_dev(rng.standard_normal(s).astype(np.float32)).to(dtype) for s in ((N, Fi), (Fi, Fo)))
+    ref = pyg.dense_transform(x, t, dtype)
+    buf = torch.empty(max(N, Fi) * Fo, dtype=dtype, device=x.device)
+    theta, out = buf[: Fi * Fo].view(Fi, Fo), buf[: N * Fo].view(N, Fo)
+    theta.copy_(t)
+    pyg.dense_transform(x, theta, dtype, out=out)
+    assert torch.equal(out, ref)
