@@ -273,18 +273,12 @@ int backward_typed(const void *grad_out, const void *x, int dtype, int64_t N, in
         f.rowptr = csr_t->rowptr, f.col = csr_t->col, f.perm = csr_t->perm, f.weight = csr_t->weight;
         f.N = N, f.E = E, f.F = F, f.chunk = csr_t->chunk;
         f.msg = PYG_MSG_SRC;
-        f.g = aggr == PYG_MEAN ? w.gscaled : grad_out;
-        f.g_dtype = aggr == PYG_MEAN ? PYG_F32 : dtype;
+        f.g = grad_out;
+        f.g_dtype = dtype;
+        f.deg_ptr = aggr == PYG_MEAN ? csr->rowptr : nullptr;
         f.x = x, f.dtype = dtype;
         f.grad_x = grad_x, f.grad_w = grad_w;
-        if (fused_backward_ok(f)) {
-            if (aggr == PYG_MEAN) {
-                k_scale_rows<T><<<grid_for(NF, kBlock * 4), kBlock, 0, s>>>(g, csr->rowptr, N, F, 1,
-                                                                            static_cast<float *>(w.gscaled));
-                PYG_LAUNCH_CHECK();
-            }
-            return fused_backward(f, w.seg, w.seg_bytes, s);
-        }
+        if (fused_backward_ok(f)) return fused_backward(f, w.seg, w.seg_bytes, s);
     }
     if (grad_w) PYG_TRY(fill<float>(grad_w, E, 0.f, s));
     if (aggr == PYG_MAX) {
@@ -350,10 +344,7 @@ int backward_typed(const void *grad_out, const void *x, int dtype, int64_t N, in
         PYG_LAUNCH_CHECK();
     }
     if (grad_w && E > 0) {
-        // fp32 mean: the scaled rows themselves, as the one-pass form reads them
-        const bool scaled = sizeof(T) == 4 && aggr == PYG_MEAN;
-        if (scaled) g = static_cast<const T *>(gs);
-        const int mean = aggr == PYG_MEAN && !scaled;
+        const int mean = aggr == PYG_MEAN;
         const int64_t kChunk = walk_chunk(E, N, 1024);
         const int64_t nchunks = (E + kChunk - 1) / kChunk;
         const unsigned grid = static_cast<unsigned>((nchunks + 3) / 4);

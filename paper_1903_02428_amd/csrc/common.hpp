@@ -273,12 +273,14 @@ int small_csr(const int64_t *src, const int64_t *dst, int64_t E, int64_t N, cons
               int32_t *col, int64_t *perm, float *w_out, hipStream_t s);
 
 // Both gradients of a weighted (msg PYG_MSG_SRC) or edge-feature propagate in
-// one pass over the reversed CSR (sum; mean with rows g already scaled).
+// one pass over the reversed CSR (sum; mean with the row bounds of csr, or of
+// edge messages with rows g already scaled).
 struct FusedBackwardArgs {
     const int64_t *rowptr;  // the reversed CSR
     const int32_t *col;
     const int64_t *perm;    // edge id of every slot
     const float *weight;    // slot order (PYG_MSG_SRC)
+    const int64_t *deg_ptr; // PYG_MSG_SRC under mean: csr's row bounds; NULL: sum
     int64_t N, E, F, chunk;
     int msg;
     const void *g;          // [N, F] in g_dtype (dtype, or fp32)

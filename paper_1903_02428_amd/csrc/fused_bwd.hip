@@ -7,7 +7,7 @@
 //   x_j + e         grad x_j += g_i            grad e = g_i
 //   max(x_j + e, 0) both times [x_j + e > 0]
 //   x_j e           grad x_j += e g_i          grad e = g_i x_j
-// (g scaled by 1 / deg_i under mean). Over the rows of the reversed CSR x_j
+// (g scaled by 1 / deg_i under mean; scalar weights divide here). Over the rows of the reversed CSR x_j
 // stays in registers, so one gather of g_i serves both; a second pass over the
 // CSR gathered x_j again and, for edge features, read every e again. The
 // per-edge arrays are reached through perm (the edge ids), loaded with the
@@ -26,6 +26,18 @@ namespace pyg {
 namespace {
 
 constexpr int kWeight = 0, kAdd = 1, kRelu = 2, kMul = 3;
+// kWeight under mean: g is the upstream row itself. grad x_j takes g_i / deg_i
+// as the scaling pass rounds it; grad w is the dot product of the unscaled rows
+// over deg_i, so that its terms carry no rounding of their own (the dot product of
+// rows scaled beforehand was 1.2 times as far from 64 bits).
+constexpr int kWeightMean = 4;
+
+// n / d, correctly rounded, from inv = 1 / d correctly rounded: one correction of
+// n * inv by its exact remainder; the fix-up settles infinities and NaN.
+__device__ __forceinline__ float div_by(float n, float d, float inv) {
+    const float q = n * inv;
+    return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-d, q, n), inv, q), d, n);
+}
 
 struct FusedParams {
     RowWalk walk;
@@ -34,7 +46,8 @@ struct FusedParams {
     int64_t F;
     const int32_t *col;
     const int64_t *perm;  // edge id of every slot
-    const float *w;       // kWeight: slot order
+    const float *w;       // kWeight, kWeightMean: slot order
+    const int64_t *deg_ptr;  // kWeightMean: the targets' row bounds [N + 1]
     const uint8_t *node_class;
     const int32_t *hot;
     const void *g;        // [N, F] of TG
@@ -51,7 +64,7 @@ struct FusedBackward {
     using LN = Lane<TG, true>;
     using R = typename LN::R;
     static constexpr int EP = LN::N;
-    static constexpr bool EDGE = KIND != kWeight;
+    static constexpr bool MEAN = KIND == kWeightMean, WEIGHT = KIND == kWeight || MEAN, EDGE = !WEIGHT;
     template <typename TE> using Share = typename std::conditional<sizeof(TE) == 4 || EP == 8, uint4, uint2>::type;
     template <typename TE>
     __device__ static __forceinline__ float share_get(const Share<TE> &r, int e) {
@@ -78,7 +91,7 @@ struct FusedBackward {
         if (KIND != kAdd && act) ldv<T, EP>(static_cast<const T *>(p.x) + r * p.F + f0, xo);
     }
     __device__ __forceinline__ void take(const int (&jj)[U], const bool (&ok)[U], const float (&ww)[U],
-                                         const int (&ee)[U]) {
+                                         const int (&ee)[U], const float (&dd)[U]) {
         R v[U];
         Share<T> ev[EDGE ? U : 1];  // raw: a lane's share of the edge row
         if constexpr (KIND == kRelu || KIND == kMul) {
@@ -95,19 +108,23 @@ struct FusedBackward {
             else if (jj[u] < 0) v[u] = LN::load_nt(src);
             else v[u] = LN::load(src);
         }
-        if constexpr (KIND == kWeight) {
-            float d[U];
+        if constexpr (WEIGHT) {
+            float d[U], inv[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 d[u] = 0.f;
+                inv[u] = MEAN ? 1.f / dd[u] : 1.f;
 #pragma unroll
                 for (int e = 0; e < EP; ++e) {
                     const float gv = LN::get(v[u], e);
                     d[u] = fmaf(gv, xo[e], d[u]);
-                    acc[e] = fmaf(ok[u] ? ww[u] : 0.f, gv, acc[e]);
+                    acc[e] = fmaf(ok[u] ? ww[u] : 0.f, MEAN ? div_by(gv, dd[u], inv[u]) : gv, acc[e]);
                 }
             }
             group_sum(d, p.lg);
+            if constexpr (MEAN)
+#pragma unroll
+                for (int u = 0; u < U; ++u) d[u] *= inv[u];
             // lane q of a sub-group stores the dot product of its q-th slot
             for (int u0 = 0; u0 < U; u0 += L) {
                 float val = d[0];
@@ -139,26 +156,31 @@ struct FusedBackward {
             }
         }
     }
-    // column (bit 31: cold), weight and edge id of slot e
-    __device__ __forceinline__ void fetch(int64_t e, int &c, float &w, int &id) const {
+    // incoming edges of node j
+    __device__ __forceinline__ float degree(int j) const {
+        return MEAN ? static_cast<float>(p.deg_ptr[j + 1] - p.deg_ptr[j]) : 1.f;
+    }
+    // column (bit 31: cold), weight, edge id and degree of slot e
+    __device__ __forceinline__ void fetch(int64_t e, int &c, float &w, int &id, float &d) const {
         c = __builtin_nontemporal_load(p.col + e);
+        d = degree(c);
         if (hot > 0 && p.node_class[c] < hot) c |= static_cast<int>(0x80000000u);
-        if constexpr (KIND == kWeight) w = __builtin_nontemporal_load(p.w + e);
+        if constexpr (WEIGHT) w = __builtin_nontemporal_load(p.w + e);
         id = static_cast<int>(__builtin_nontemporal_load(p.perm + e));
     }
     __device__ __forceinline__ void run(int64_t r, int64_t s, int64_t t, int kind, int64_t slot) {
         begin(r);
         int nc = 0, ni = 0;
-        float nw = 0.f;
-        if (s + lane < t) fetch(s + lane, nc, nw, ni);
+        float nw = 0.f, nd = 1.f;
+        if (s + lane < t) fetch(s + lane, nc, nw, ni, nd);
         for (int64_t base = s; base < t; base += kWave) {
             const int n = static_cast<int>(uniform64((t - base) < kWave ? (t - base) : kWave));
             const int mc = nc, mi = ni;
-            const float mw = nw;
-            if (base + kWave + lane < t) fetch(base + kWave + lane, nc, nw, ni);
+            const float mw = nw, md = nd;
+            if (base + kWave + lane < t) fetch(base + kWave + lane, nc, nw, ni, nd);
             for (int st = 0; st < n; st += S * U) {
                 int jj[U], ee[U];
-                float ww[U];
+                float ww[U], dd[U];
                 bool ok[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
@@ -166,10 +188,12 @@ struct FusedBackward {
                     ok[u] = idx < n;
                     jj[u] = __shfl(mc, idx & (kWave - 1), kWave);
                     ee[u] = __shfl(mi, idx & (kWave - 1), kWave);
-                    if constexpr (KIND == kWeight) ww[u] = __shfl(mw, idx & (kWave - 1), kWave);
+                    if constexpr (WEIGHT) ww[u] = __shfl(mw, idx & (kWave - 1), kWave);
                     else ww[u] = 0.f;
+                    dd[u] = 1.f;
+                    if constexpr (MEAN) dd[u] = __shfl(md, idx & (kWave - 1), kWave);
                 }
-                take(jj, ok, ww, ee);
+                take(jj, ok, ww, ee, dd);
             }
         }
         for (int off = L; off < kWave; off <<= 1)
@@ -184,16 +208,17 @@ struct FusedBackward {
         begin(r);
         for (int64_t b = s; b < t; b += U) {
             int jj[U], ee[U];
-            float ww[U];
+            float ww[U], dd[U];
             bool ok[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 ok[u] = b + u < t;
                 jj[u] = ok[u] ? p.col[b + u] : 0;
                 ee[u] = ok[u] ? static_cast<int>(p.perm[b + u]) : 0;
-                ww[u] = (KIND == kWeight && ok[u]) ? p.w[b + u] : 0.f;
+                ww[u] = (WEIGHT && ok[u]) ? p.w[b + u] : 0.f;
+                dd[u] = ok[u] ? degree(jj[u]) : 1.f;
             }
-            take(jj, ok, ww, ee);
+            take(jj, ok, ww, ee, dd);
         }
         if (act) stv<T, EP>(static_cast<T *>(p.grad_x) + r * p.F + f0, acc);
     }
@@ -238,7 +263,7 @@ FusedWs carve_fused(void *base, int64_t N, int64_t F, int64_t E, int64_t chunk) 
 
 template <typename TG, typename T, int KIND>
 int launch_fused(const FusedParams &p, hipStream_t s) {
-    constexpr int U = KIND == kWeight ? 4 : 2;  // slots in flight per lane: registers, and with them wavefronts, count for more
+    constexpr int U = KIND == kWeight || KIND == kWeightMean ? 4 : 2;  // slots in flight per lane: registers, and with them wavefronts, count for more
     const unsigned grid = static_cast<unsigned>((p.zero_items + p.walk.nchunks + 3) / 4);
     if (p.lg < 6 && p.walk.E <= kLightMaxDegree * p.walk.N)
         k_fused_backward<TG, T, KIND, U, true><<<grid, kBlock, 0, s>>>(p);
@@ -252,6 +277,8 @@ template <typename TG, typename T>
 int launch_kind(const FusedParams &p, int kind, hipStream_t s) {
     if constexpr (sizeof(TG) == sizeof(T)) {
         if (kind == kWeight) return launch_fused<TG, T, kWeight>(p, s);
+        if constexpr (sizeof(T) == 4)
+            if (kind == kWeightMean) return launch_fused<TG, T, kWeightMean>(p, s);
     }
     if (kind == kAdd) return launch_fused<TG, T, kAdd>(p, s);
     if (kind == kRelu) return launch_fused<TG, T, kRelu>(p, s);
@@ -270,7 +297,9 @@ bool fused_backward_ok(const FusedBackwardArgs &a) {
     const int64_t ep = a.g_dtype == PYG_BF16 ? 8 : 4;
     const int64_t sz = a.dtype == PYG_BF16 ? 2 : 4;
     auto al = [](const void *q, int64_t b) { return reinterpret_cast<uintptr_t>(q) % b == 0; };
-    // (weights: g in the type of x, as the dot products of the pass over the CSR take it)
+    // (weights: g in the type of x, as the dot products of the pass over the CSR
+    // take it; a bf16 mean sums fp32 rows, 4 features a lane: the separate kernels)
+    if (a.deg_ptr && a.dtype != PYG_F32) return false;
     return a.E > 0 && a.F > 0 && (a.msg != PYG_MSG_SRC || a.g_dtype == a.dtype) && a.F % ep == 0 && a.F / ep <= kWave && a.perm && al(a.g, 16) && al(a.x, ep * sz) &&
            al(a.edge_attr, ep * sz) && al(a.grad_x, ep * sz) && al(a.grad_e, ep * sz);
 }
@@ -297,7 +326,8 @@ int fused_backward(const FusedBackwardArgs &a, void *ws, size_t ws_bytes, hipStr
         p.hot = w.hot;
     }
     const int kind = a.msg == PYG_MSG_EDGE_ADD ? kAdd : a.msg == PYG_MSG_EDGE_RELU ? kRelu
-                     : a.msg == PYG_MSG_EDGE_MUL ? kMul : kWeight;
+                     : a.msg == PYG_MSG_EDGE_MUL ? kMul : a.deg_ptr ? kWeightMean : kWeight;
+    p.deg_ptr = a.deg_ptr;
     if (a.g_dtype == PYG_BF16) PYG_TRY((launch_kind<uint16_t, uint16_t>(p, kind, s)));
     else if (a.dtype == PYG_BF16) PYG_TRY((launch_kind<float, uint16_t>(p, kind, s)));
     else PYG_TRY((launch_kind<float, float>(p, kind, s)));
