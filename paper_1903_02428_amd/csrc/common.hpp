@@ -264,6 +264,8 @@ int hot_rows(const int64_t *rowptr, int64_t n_rows, int64_t row_bytes, int32_t *
 size_t segment_blocked_workspace(int64_t E, int64_t n_rows, int64_t F, int64_t B, int aggr, int64_t chunk);
 int segment_reduce_blocked(const SegmentArgs &a, int64_t B, void *ws, size_t ws_bytes, hipStream_t s);
 size_t segment_workspace(int64_t E, int64_t F, int aggr, int64_t chunk, int64_t n_rows);
+// Whether rows of these sizes are summed in windows of 128 bytes, eight slots at a time.
+bool segment_windows(int64_t n_rows, int64_t row_bytes);
 int segment_reduce(const SegmentArgs &a, void *ws, size_t ws_bytes, hipStream_t s);
 
 // The plain CSR of a small edge list in one launch (no workspace); w_out is

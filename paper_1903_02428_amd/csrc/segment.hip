@@ -1061,8 +1061,7 @@ int run_typed(const SegmentArgs &a, SegParams p, hipStream_t s) {
     // plain messages, vector lanes, rows wider than a window, large in total
     const bool narrow = kWindowBytes > 0 && vec && !ident &&
                         (PYG_NARROW_ALL || mk == kMsgSrc || mk == kMsgWeighted || mk == kMsgDiff || mk == kMsgGcn) &&
-                        row_bytes > kWindowBytes &&
-                        row_bytes % kWindowBytes == 0 && a.n_rows * row_bytes >= kWindowMinBytes;
+                        segment_windows(a.n_rows, row_bytes);
     // cache hint: only when the source rows do not fit in L2 (row in-degree as the hotness proxy)
     p.hot_class = nullptr;
     const int64_t hint_bytes = narrow && PYG_HINT_NARROW == 1 ? kWindowBytes : row_bytes;
@@ -1526,6 +1525,11 @@ int64_t segment_chunk(int64_t E, int64_t n_rows, int64_t requested) {
 
 size_t segment_workspace(int64_t E, int64_t F, int aggr, int64_t chunk, int64_t n_rows) {
     return carve_segment(nullptr, E, F, aggr, segment_chunk(E, n_rows, chunk), n_rows).bytes;
+}
+
+bool segment_windows(int64_t n_rows, int64_t row_bytes) {
+    return kWindowBytes > 0 && row_bytes > kWindowBytes && row_bytes % kWindowBytes == 0 &&
+           n_rows * row_bytes >= kWindowMinBytes;
 }
 
 int segment_reduce(const SegmentArgs &a, void *ws, size_t ws_bytes, hipStream_t s) {
