@@ -233,12 +233,31 @@ static inline int64_t light_row_slots(int64_t E, int64_t n_rows, int64_t chunk) 
     return m < chunk ? m : chunk;
 }
 
+// Pieces of a row up to which one wavefront folds it (two rounds of eight in
+// flight); more are split over a workgroup's wavefronts.
+constexpr int kFoldWave = 16;
+// Pieces of the long row that ends at slot `end` and starts in chunk c (a CSR
+// has fewer than 2^31 slots, and so has a chunk that a row is longer than).
+__device__ __forceinline__ int32_t pieces_of(int64_t end, int64_t chunk, int64_t c) {
+    return static_cast<int32_t>(static_cast<uint32_t>(end - 1) / static_cast<uint32_t>(chunk) - static_cast<uint32_t>(c)) + 1;
+}
 // Chunks one wavefront of a fold launch looks at: enough wavefronts first.
 constexpr int kFoldPerMax = 16;
 static inline int fold_per(int64_t nchunks) {
     const int64_t per = nchunks / 8192;
     return per < 1 ? 1 : per > kFoldPerMax ? kFoldPerMax : static_cast<int>(per);
 }
+// Its grid: a wavefront per group of 64 features (blockIdx.y) of that many chunks.
+struct FoldGrid {
+    int per;
+    dim3 grid;
+    FoldGrid(int64_t nchunks, int64_t features) {
+        int64_t groups = (features + kWave - 1) / kWave;
+        groups = groups < 1 ? 1 : groups > 65535 ? 65535 : groups;
+        per = fold_per(nchunks * groups);
+        grid = dim3(grid_for(nchunks, per * (kBlock / kWave), 1 << 30), static_cast<unsigned>(groups));
+    }
+};
 
 // Folds the pieces of the long rows (sum): part [2 * nchunks, F] and head_row
 // [nchunks] as the segment kernel's walk writes them.

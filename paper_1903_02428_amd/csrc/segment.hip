@@ -849,12 +849,15 @@ __global__ __launch_bounds__(WAVES * kWave) void k_segment_fixup_grouped(SegPara
 }
 
 // The fold of ordinary graphs. A wavefront looks at `per` chunks at once (a
-// lane each) and folds the long rows that start in them one after another, a
-// lane per feature and eight pieces in flight; a row of more than kFoldGroup
-// pieces is left to the whole workgroup afterwards. One workgroup per chunk,
-// nearly all of them with nothing to fold, took 44 us on the large power-law
-// graph's 112,000 chunks; with 16 chunks per wavefront 25 us. Graphs of few chunks
-// keep a wavefront per chunk (fold_per in common.hpp).
+// lane each) and folds the long rows that start in them one after another,
+// eight pieces in flight, a lane for each of the 64 features that blockIdx.y
+// gives it; a row of more than kFoldWave pieces is left to the whole
+// workgroup afterwards. One workgroup per chunk, nearly all of them with
+// nothing to fold, took 44 us on the large power-law graph's 112,000 chunks;
+// with 16 chunks per wavefront 25 us. Graphs of few chunks keep a wavefront per
+// chunk and 64 features (fold_per in common.hpp). All features of a row in one
+// wavefront were eight passes in series at F = 500 (108k edges: the whole sum
+// 58.7 us, 44.8 spread over wavefronts; 48.6 by a workgroup per chunk).
 template <typename T, bool MAXA, bool OF32>
 __global__ __launch_bounds__(kBlock) void k_segment_fixup(SegParams p, int per) {
     constexpr int kW = kBlock / kWave;
@@ -863,12 +866,15 @@ __global__ __launch_bounds__(kBlock) void k_segment_fixup(SegParams p, int per) 
     __shared__ int32_t big_row[kW * kFoldPerMax];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int64_t c0 = ((int64_t)blockIdx.x * kW + wave) * per;
+    // features of this workgroup: group blockIdx.y of 64, and every gridDim.y-th from there
+    const int64_t f_end = p.fbase + p.fcnt, f_first = p.fbase + (int64_t)blockIdx.y * kWave;
+    const int64_t f_step = (int64_t)gridDim.y * kWave;
     int32_t row = -1, K = 0;
     if (lane < per && c0 + lane < p.nchunks) {
         row = p.head_row[c0 + lane];
-        if (row >= 0) K = static_cast<int32_t>((p.rowptr[row + 1] - 1) / p.chunk - (c0 + lane) + 1);
+        if (row >= 0) K = pieces_of(p.rowptr[row + 1], p.chunk, c0 + lane);
     }
-    const bool big = K > kFoldGroup;
+    const bool big = K > kFoldWave;
     if (lane < per) big_row[wave * per + lane] = big ? row : -1;
     uint64_t hit = __ballot(row >= 0 && !big);
     T *out = static_cast<T *>(p.out);
@@ -877,7 +883,7 @@ __global__ __launch_bounds__(kBlock) void k_segment_fixup(SegParams p, int per) 
         hit &= hit - 1;
         const int64_t c = c0 + k, r = __builtin_amdgcn_readlane(row, k);
         const int n = __builtin_amdgcn_readlane(K, k);
-        for (int64_t f = p.fbase + lane; f < p.fbase + p.fcnt; f += kWave) {
+        for (int64_t f = f_first + lane; f < f_end; f += f_step) {
             // sums in four ranges of the pieces, then over the ranges: the order
             // (and the shorter rounding chains) of a workgroup's four waves
             float v = 0.f, total = 0.f;
@@ -912,9 +918,17 @@ __global__ __launch_bounds__(kBlock) void k_segment_fixup(SegParams p, int per) 
         }
     }
     __syncthreads();
-    for (int k = 0; k < kW * per; ++k) {
+    // the workgroup's long rows (kW * per is at most a wavefront): uniform over it
+    hit = __ballot(lane < kW * per && big_row[lane] >= 0);
+    while (hit) {
+        const int k = __ffsll(static_cast<unsigned long long>(hit)) - 1;
+        hit &= hit - 1;
         const int64_t r = big_row[k];
-        if (r >= 0) fold_long_row<T, MAXA, kW, 8, OF32>(p, (int64_t)blockIdx.x * kW * per + k, r, sv, sp);
+        for (int64_t f = f_first; f < f_end; f += f_step) {
+            p.fbase = f;
+            p.fcnt = f_end - f < kWave ? f_end - f : kWave;
+            fold_long_row<T, MAXA, kW, 8, OF32>(p, (int64_t)blockIdx.x * kW * per + k, r, sv, sp);
+        }
     }
 }
 
@@ -985,8 +999,8 @@ int launch_fixup(const SegParams &p, hipStream_t s) {
         PYG_LAUNCH_CHECK();
         k_segment_fixup_grouped<T, MAXA, 16, OF32><<<static_cast<unsigned>(p.nchunks), 16 * kWave, 0, s>>>(p);
     } else {
-        const int per = fold_per(p.nchunks);
-        k_segment_fixup<T, MAXA, OF32><<<grid_for(p.nchunks, per * (kBlock / kWave), 1 << 26), kBlock, 0, s>>>(p, per);
+        const FoldGrid g(p.nchunks, p.fcnt);
+        k_segment_fixup<T, MAXA, OF32><<<g.grid, kBlock, 0, s>>>(p, g.per);
     }
     PYG_LAUNCH_CHECK();
     return PYG_OK;
