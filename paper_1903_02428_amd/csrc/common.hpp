@@ -241,21 +241,37 @@ constexpr int kFoldWave = 16;
 __device__ __forceinline__ int32_t pieces_of(int64_t end, int64_t chunk, int64_t c) {
     return static_cast<int32_t>(static_cast<uint32_t>(end - 1) / static_cast<uint32_t>(chunk) - static_cast<uint32_t>(c)) + 1;
 }
-// Chunks one wavefront of a fold launch looks at: enough wavefronts first.
+// The grid of a fold: a workgroup per group of 64 features of 4 * `per` chunks
+// (group-major: every XCD meets every group), one chunk per wavefront while
+// there are fewer than 8,192 of them. whole_rows: the first group's workgroups
+// take all features of short rows, the others look for long rows alone, in as
+// many chunks as they can.
 constexpr int kFoldPerMax = 16;
-static inline int fold_per(int64_t nchunks) {
-    const int64_t per = nchunks / 8192;
-    return per < 1 ? 1 : per > kFoldPerMax ? kFoldPerMax : static_cast<int>(per);
-}
-// Its grid: a wavefront per group of 64 features (blockIdx.y) of that many chunks.
 struct FoldGrid {
+    int per, per_rest;
+    unsigned sets, sets_rest, grid;  // sets of 4 * per chunks
+    FoldGrid(int64_t nchunks, int64_t features, bool whole_rows = false) {
+        const int64_t g = (features + kWave - 1) / kWave, want = nchunks * (whole_rows ? 1 : g) / 8192;
+        per = want < 1 ? 1 : want > kFoldPerMax ? kFoldPerMax : static_cast<int>(want);
+        per_rest = whole_rows ? kFoldPerMax : per;
+        sets = grid_for(nchunks, per * (kBlock / kWave), 1 << 23);
+        sets_rest = grid_for(nchunks, per_rest * (kBlock / kWave), 1 << 23);
+        const int64_t most = ((int64_t(1) << 23) - sets) / sets_rest;  // a launch is below 2^32 threads: else groups take turns
+        grid = sets + sets_rest * static_cast<unsigned>(g <= 1 ? 0 : g - 1 < most ? g - 1 : most);
+    }
+};
+// A workgroup's place in it: its chunks from `first` on, its group of features
+// and how many groups there are.
+struct FoldPlace {
     int per;
-    dim3 grid;
-    FoldGrid(int64_t nchunks, int64_t features) {
-        int64_t groups = (features + kWave - 1) / kWave;
-        groups = groups < 1 ? 1 : groups > 65535 ? 65535 : groups;
-        per = fold_per(nchunks * groups);
-        grid = dim3(grid_for(nchunks, per * (kBlock / kWave), 1 << 30), static_cast<unsigned>(groups));
+    int64_t first, group, groups;
+    __device__ __forceinline__ explicit FoldPlace(const FoldGrid &g) {
+        const unsigned b = blockIdx.x, rest = b - g.sets;
+        const bool head = b < g.sets;
+        per = head ? g.per : g.per_rest;
+        group = head ? 0 : 1 + rest / g.sets_rest;
+        first = (int64_t)(head ? b : rest % g.sets_rest) * (kBlock / kWave) * per;
+        groups = 1 + (g.grid - g.sets) / g.sets_rest;
     }
 };
 

@@ -259,60 +259,118 @@ __global__ __launch_bounds__(kBlock) void k_gat_forward(GatParams p) {
     else walk_heavy(p.walk, c, lane, op);
 }
 
-// The pieces of every long row, in chunk order, rescaled to the maximum so far. One wavefront looks at `per` chunks and takes the
-// long rows that start in them, a lane per feature.
+// Where wavefront w's quarter of n pieces begins.
+__device__ __forceinline__ int first_piece(int n, int w) { return static_cast<int>(static_cast<int64_t>(n) * w / (kBlock / kWave)); }
+
+// Pieces m0 .. m1 - 1 of a long row (head chunk c), one feature per lane: sums
+// rescaled to the largest maximum so far, four pieces in flight; LONG: each 16
+// pieces are summed by themselves before they join the rest.
+struct GatState {
+    float m, z, zp, a, b;
+    __device__ __forceinline__ void rescale(float mx) {
+        const float k = pexp(m, mx);
+        z *= k, zp *= k, a *= k, b *= k;
+        m = mx;
+    }
+    __device__ __forceinline__ void add(float k, const GatState &o) {
+        z = fmaf(k, o.z, z), zp = fmaf(k, o.zp, zp), a = fmaf(k, o.a, a), b = fmaf(k, o.b, b);
+    }
+};
+template <bool GRAD, bool LONG>
+__device__ __forceinline__ GatState fold_pieces(const GatParams &p, int64_t c, int m0, int m1, int64_t f, int64_t h) {
+    constexpr int U = 4;
+    GatState some{-INFINITY, 0.f, 0.f, 0.f, 0.f}, all = some;  // one maximum for both: some.m
+    for (int i0 = m0; i0 < m1; i0 += U) {
+        GatState t[U];
+        float mx = some.m;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool on = i0 + u < m1;
+            const int64_t sl = piece_of(c, i0 + u);
+            const float4 st = on ? p.part_st[sl * p.H + h] : make_float4(-INFINITY, 0.f, 0.f, 0.f);
+            t[u] = {st.x, st.y, st.z, on ? p.part[sl * p.F + f] : 0.f, GRAD && on ? p.part_plus[sl * p.F + f] : 0.f};
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) mx = fmaxf(mx, t[u].m);
+        if constexpr (LONG) all.m = some.m, all.rescale(mx);
+        some.rescale(mx);
+#pragma unroll
+        for (int u = 0; u < U; ++u) some.add(pexp(t[u].m, mx), t[u]);
+        if (LONG && ((i0 - m0) & 12) == 12) all.add(1.f, some), some = {mx, 0.f, 0.f, 0.f, 0.f};
+    }
+    if constexpr (LONG) some.add(1.f, all);
+    return some;
+}
+
+// Per long row and feature the sums over its pieces. A wavefront looks at
+// `per` chunks and folds the long rows that start in them; rows of more than
+// kFoldWave pieces are left to the workgroup, whose wavefronts take a quarter
+// of the pieces each (a hub of 500,000 of 2M edges, 8 heads of 32: 4.8 ms in one
+// wavefront, 0.4 ms so). A workgroup has a
+// group of 64 features of its long rows. The short ones are split like that
+// (`split`) only while there are too few chunks to fill the chip; else the
+// first group's workgroup takes whole rows (20,000 rows of 150 slots in two
+// pieces, 8 heads of 32: 34 us, 50 split, as every part finds the rows again).
+inline bool fold_split(int64_t nchunks) { return nchunks < 8192; }
+
 template <typename T, bool GRAD>
-__global__ __launch_bounds__(kBlock) void k_gat_fold(GatParams p, int per) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t w = uniform64((int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave);
-    const int64_t c0 = w * per;
-    if (c0 >= p.walk.nchunks) return;
-    const int32_t mine = (lane < per && c0 + lane < p.walk.nchunks) ? p.walk.head_row[c0 + lane] : -1;
-    uint64_t hit = __ballot(mine >= 0);
+__global__ __launch_bounds__(kBlock) void k_gat_fold(GatParams p, FoldGrid grid, bool split) {
+    constexpr int kW = kBlock / kWave;
+    __shared__ GatState part[kW][kWave];
+    __shared__ int32_t big_row[kW * kFoldPerMax];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const FoldPlace at(grid);
+    const int per = at.per;
+    const int64_t c0 = uniform64(at.first + wave * per), f_first = at.group * kWave, step = at.groups * kWave;
+    int32_t row = -1, K = 0;
+    if (lane < per && c0 + lane < p.walk.nchunks) {
+        row = p.walk.head_row[c0 + lane];
+        if (row >= 0) K = pieces_of(p.walk.rowptr[row + 1], p.walk.chunk, c0 + lane);
+    }
+    const bool big = K > kFoldWave;
+    if (lane < per) big_row[wave * per + lane] = big ? row : -1;
+    uint64_t hit = __ballot(row >= 0 && !big && (split || f_first == 0));
     const int64_t C = p.F / p.H;
+    auto store = [&](int64_t r, int64_t f, int64_t h, const GatState &s) {
+        const float inv = 1.f / s.z;
+        if constexpr (sizeof(T) == 2) static_cast<T *>(p.out)[r * p.F + f] = f32_to_bf16_rne(s.a * inv);
+        else static_cast<T *>(p.out)[r * p.F + f] = s.a * inv;
+        if constexpr (GRAD) {
+            p.all[r * p.F + f] = s.a * inv;
+            p.plus[r * p.F + f] = s.b * inv;
+            if (f == h * C) p.stat[r * p.H + h] = make_float4(p.a_dst[r * p.H + h], s.m, inv, s.zp / s.z);
+        }
+    };
     while (hit) {
         const int k = __ffsll(static_cast<unsigned long long>(hit)) - 1;
         hit &= hit - 1;
-        const int64_t c = c0 + k, r = __builtin_amdgcn_readlane(mine, k);
-        const int64_t K = (uniform64(p.walk.rowptr[r + 1]) - 1) / p.walk.chunk - c + 1;
-        for (int64_t f = lane; f < p.F; f += kWave) {
-            const int64_t h = f / C;
-            float m = -INFINITY, z = 0.f, zp = 0.f, a = 0.f, b = 0.f;
-            for (int64_t i0 = 0; i0 < K; i0 += 4) {  // four pieces in flight
-                float4 st[4];
-                float pa[4], pb[4];
-                float mx = m;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int64_t sl = piece_of(c, i0 + u);
-                    const bool on = i0 + u < K;
-                    st[u] = on ? p.part_st[sl * p.H + h] : make_float4(-INFINITY, 0.f, 0.f, 0.f);
-                    pa[u] = on ? p.part[sl * p.F + f] : 0.f;
-                    if constexpr (GRAD) pb[u] = on ? p.part_plus[sl * p.F + f] : 0.f;
+        const int64_t r = __builtin_amdgcn_readlane(row, k);
+        const int n = __builtin_amdgcn_readlane(K, k);
+        for (int64_t f = (split ? f_first : 0) + lane; f < p.F; f += split ? step : kWave)
+            store(r, f, f / C, fold_pieces<GRAD, false>(p, c0 + k, 0, n, f, f / C));
+    }
+    __syncthreads();
+    // the workgroup's long rows (kW * per is at most a wavefront): uniform over it
+    hit = __ballot(lane < kW * per && big_row[lane] >= 0);
+    while (hit) {
+        const int k = __ffsll(static_cast<unsigned long long>(hit)) - 1;
+        hit &= hit - 1;
+        const int64_t r = big_row[k], c = at.first + k;
+        const int n = pieces_of(p.walk.rowptr[r + 1], p.walk.chunk, c);
+        for (int64_t fg = f_first; fg < p.F; fg += step) {
+            const int64_t f = fg + lane, h = f < p.F ? f / C : 0;
+            if (f < p.F) part[wave][lane] = fold_pieces<GRAD, true>(p, c, first_piece(n, wave), first_piece(n, wave + 1), f, h);
+            __syncthreads();
+            if (wave == 0 && f < p.F) {
+                GatState s = part[0][lane];
+                for (int w = 1; w < kW; ++w) {
+                    const GatState o = part[w][lane];
+                    s.rescale(fmaxf(s.m, o.m));
+                    s.add(pexp(o.m, s.m), o);
                 }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) mx = fmaxf(mx, st[u].x);
-                const float s0 = pexp(m, mx);
-                z *= s0, zp *= s0, a *= s0;
-                if constexpr (GRAD) b *= s0;
-                m = mx;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const float s = pexp(st[u].x, m);
-                    z = fmaf(s, st[u].y, z);
-                    zp = fmaf(s, st[u].z, zp);
-                    a = fmaf(s, pa[u], a);
-                    if constexpr (GRAD) b = fmaf(s, pb[u], b);
-                }
+                store(r, f, h, s);
             }
-            const float inv = 1.f / z;
-            if constexpr (sizeof(T) == 2) static_cast<T *>(p.out)[r * p.F + f] = f32_to_bf16_rne(a * inv);
-            else static_cast<T *>(p.out)[r * p.F + f] = a * inv;
-            if constexpr (GRAD) {
-                p.all[r * p.F + f] = a * inv;
-                p.plus[r * p.F + f] = b * inv;
-                if (f == h * C) p.stat[r * p.H + h] = make_float4(p.a_dst[r * p.H + h], m, inv, zp / z);
-            }
+            __syncthreads();
         }
     }
 }
@@ -493,28 +551,74 @@ __global__ __launch_bounds__(kBlock) void k_gat_backward(GatParams p) {
     else walk_heavy(p.walk, c, lane, op);
 }
 
+// The pieces of every long row: the F features, then the H sums of dv, split
+// as in k_gat_fold. (One wavefront and one chain for a row of whatever length:
+// the output of a hub of 150,000 edges was 9e-7 from 64 bits, below 3e-7 split.)
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_gat_backward_fold(GatParams p, int per) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t w = uniform64((int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave);
-    const int64_t c0 = w * per;
-    if (c0 >= p.walk.nchunks) return;
-    const int32_t mine = (lane < per && c0 + lane < p.walk.nchunks) ? p.walk.head_row[c0 + lane] : -1;
-    uint64_t hit = __ballot(mine >= 0);
+__global__ __launch_bounds__(kBlock) void k_gat_backward_fold(GatParams p, FoldGrid grid, bool split) {
+    constexpr int kW = kBlock / kWave;
+    __shared__ float part[kW][kWave];
+    __shared__ int32_t big_row[kW * kFoldPerMax];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const FoldPlace at(grid);
+    const int per = at.per;
+    const int64_t c0 = uniform64(at.first + wave * per), f_first = at.group * kWave, step = at.groups * kWave;
+    int32_t row = -1, K = 0;
+    if (lane < per && c0 + lane < p.walk.nchunks) {
+        row = p.walk.head_row[c0 + lane];
+        if (row >= 0) K = pieces_of(p.walk.rowptr[row + 1], p.walk.chunk, c0 + lane);
+    }
+    const bool big = K > kFoldWave;
+    if (lane < per) big_row[wave * per + lane] = big ? row : -1;
+    uint64_t hit = __ballot(row >= 0 && !big && (split || f_first == 0));
+    const int64_t cols = p.F + p.H;
+    // pieces m0 .. m1 - 1, each 16 summed by themselves
+    auto fold = [&](int64_t c, int m0, int m1, int64_t f) {
+        constexpr int U = 8;
+        const float *src = f < p.F ? p.part + f : p.part_gs + (f - p.F);
+        const int64_t stride = f < p.F ? p.F : p.H;
+        float all = 0.f, some = 0.f;
+        for (int i0 = m0; i0 < m1; i0 += U) {
+            float v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = i0 + u < m1 ? src[piece_of(c, i0 + u) * stride] : 0.f;
+#pragma unroll
+            for (int u = 0; u < U; ++u) some += v[u];
+            if ((i0 - m0) & U) all += some, some = 0.f;
+        }
+        return all + some;
+    };
+    auto store = [&](int64_t r, int64_t f, float v) {
+        if (f >= p.F) p.grad_src[r * p.H + f - p.F] = v;
+        else if constexpr (sizeof(T) == 2) static_cast<T *>(p.grad_x)[r * p.F + f] = f32_to_bf16_rne(v);
+        else static_cast<T *>(p.grad_x)[r * p.F + f] = v;
+    };
     while (hit) {
         const int k = __ffsll(static_cast<unsigned long long>(hit)) - 1;
         hit &= hit - 1;
-        const int64_t c = c0 + k, r = __builtin_amdgcn_readlane(mine, k);
-        const int64_t K = (uniform64(p.walk.rowptr[r + 1]) - 1) / p.walk.chunk - c + 1;
-        for (int64_t f = lane; f < p.F + p.H; f += kWave) {  // the F features, then the H sums of dv
-            const float *src = f < p.F ? p.part + f : p.part_gs + (f - p.F);
-            const int64_t stride = f < p.F ? p.F : p.H;
-            float a = 0.f;
-#pragma unroll 8
-            for (int64_t i = 0; i < K; ++i) a += src[piece_of(c, i) * stride];
-            if (f >= p.F) p.grad_src[r * p.H + f - p.F] = a;
-            else if constexpr (sizeof(T) == 2) static_cast<T *>(p.grad_x)[r * p.F + f] = f32_to_bf16_rne(a);
-            else static_cast<T *>(p.grad_x)[r * p.F + f] = a;
+        const int64_t r = __builtin_amdgcn_readlane(row, k);
+        const int n = __builtin_amdgcn_readlane(K, k);
+        for (int64_t f = (split ? f_first : 0) + lane; f < cols; f += split ? step : kWave)
+            store(r, f, fold(c0 + k, 0, n, f));
+    }
+    __syncthreads();
+    // the workgroup's long rows (kW * per is at most a wavefront): uniform over it
+    hit = __ballot(lane < kW * per && big_row[lane] >= 0);
+    while (hit) {
+        const int k = __ffsll(static_cast<unsigned long long>(hit)) - 1;
+        hit &= hit - 1;
+        const int64_t r = big_row[k], c = at.first + k;
+        const int n = pieces_of(p.walk.rowptr[r + 1], p.walk.chunk, c);
+        for (int64_t fg = f_first; fg < cols; fg += step) {
+            const int64_t f = fg + lane;
+            if (f < cols) part[wave][lane] = fold(c, first_piece(n, wave), first_piece(n, wave + 1), f);
+            __syncthreads();
+            if (wave == 0 && f < cols) {
+                float v = part[0][lane];
+                for (int w = 1; w < kW; ++w) v += part[w][lane];
+                store(r, f, v);
+            }
+            __syncthreads();
         }
     }
 }
@@ -599,8 +703,8 @@ int launch_forward(const GatParams &p, hipStream_t s) {
     else k_gat_forward<T, U, GRAD, false><<<grid, kBlock, 0, s>>>(p);
     PYG_LAUNCH_CHECK();
     if (p.walk.nchunks > 1) {
-        const int per = fold_per(p.walk.nchunks);
-        k_gat_fold<T, GRAD><<<grid_for(p.walk.nchunks, 4 * per, 1 << 26), kBlock, 0, s>>>(p, per);
+        const FoldGrid g(p.walk.nchunks, p.F, !fold_split(p.walk.nchunks));
+        k_gat_fold<T, GRAD><<<g.grid, kBlock, 0, s>>>(p, g, fold_split(p.walk.nchunks));
         PYG_LAUNCH_CHECK();
     }
     return PYG_OK;
@@ -621,8 +725,8 @@ int launch_backward(const GatParams &p, const float *all, const float *plus, con
     else k_gat_backward<T, U, false><<<grid, kBlock, 0, s>>>(p);
     PYG_LAUNCH_CHECK();
     if (p.walk.nchunks > 1) {
-        const int per = fold_per(p.walk.nchunks);
-        k_gat_backward_fold<T><<<grid_for(p.walk.nchunks, 4 * per, 1 << 26), kBlock, 0, s>>>(p, per);
+        const FoldGrid g(p.walk.nchunks, p.F + p.H, !fold_split(p.walk.nchunks));
+        k_gat_backward_fold<T><<<g.grid, kBlock, 0, s>>>(p, g, fold_split(p.walk.nchunks));
         PYG_LAUNCH_CHECK();
     }
     return PYG_OK;

@@ -850,25 +850,26 @@ __global__ __launch_bounds__(WAVES * kWave) void k_segment_fixup_grouped(SegPara
 
 // The fold of ordinary graphs. A wavefront looks at `per` chunks at once (a
 // lane each) and folds the long rows that start in them one after another,
-// eight pieces in flight, a lane for each of the 64 features that blockIdx.y
-// gives it; a row of more than kFoldWave pieces is left to the whole
+// eight pieces in flight, a lane for each of its workgroup's 64
+// features; a row of more than kFoldWave pieces is left to the whole
 // workgroup afterwards. One workgroup per chunk, nearly all of them with
 // nothing to fold, took 44 us on the large power-law graph's 112,000 chunks;
 // with 16 chunks per wavefront 25 us. Graphs of few chunks keep a wavefront per
-// chunk and 64 features (fold_per in common.hpp). All features of a row in one
+// chunk and 64 features (FoldGrid in common.hpp). All features of a row in one
 // wavefront were eight passes in series at F = 500 (108k edges: the whole sum
 // 58.7 us, 44.8 spread over wavefronts; 48.6 by a workgroup per chunk).
 template <typename T, bool MAXA, bool OF32>
-__global__ __launch_bounds__(kBlock) void k_segment_fixup(SegParams p, int per) {
+__global__ __launch_bounds__(kBlock) void k_segment_fixup(SegParams p, FoldGrid grid) {
     constexpr int kW = kBlock / kWave;
     __shared__ float sv[kW][kWave];
     __shared__ int32_t sp[kW][kWave];
     __shared__ int32_t big_row[kW * kFoldPerMax];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    const int64_t c0 = ((int64_t)blockIdx.x * kW + wave) * per;
-    // features of this workgroup: group blockIdx.y of 64, and every gridDim.y-th from there
-    const int64_t f_end = p.fbase + p.fcnt, f_first = p.fbase + (int64_t)blockIdx.y * kWave;
-    const int64_t f_step = (int64_t)gridDim.y * kWave;
+    const FoldPlace at(grid);
+    const int per = at.per;
+    const int64_t c0 = at.first + wave * per;
+    // features of this workgroup: its group of 64, and every groups-th from there
+    const int64_t f_end = p.fbase + p.fcnt, f_first = p.fbase + at.group * kWave, f_step = at.groups * kWave;
     int32_t row = -1, K = 0;
     if (lane < per && c0 + lane < p.nchunks) {
         row = p.head_row[c0 + lane];
@@ -927,7 +928,7 @@ __global__ __launch_bounds__(kBlock) void k_segment_fixup(SegParams p, int per) 
         for (int64_t f = f_first; f < f_end; f += f_step) {
             p.fbase = f;
             p.fcnt = f_end - f < kWave ? f_end - f : kWave;
-            fold_long_row<T, MAXA, kW, 8, OF32>(p, (int64_t)blockIdx.x * kW * per + k, r, sv, sp);
+            fold_long_row<T, MAXA, kW, 8, OF32>(p, at.first + k, r, sv, sp);
         }
     }
 }
@@ -1000,7 +1001,7 @@ int launch_fixup(const SegParams &p, hipStream_t s) {
         k_segment_fixup_grouped<T, MAXA, 16, OF32><<<static_cast<unsigned>(p.nchunks), 16 * kWave, 0, s>>>(p);
     } else {
         const FoldGrid g(p.nchunks, p.fcnt);
-        k_segment_fixup<T, MAXA, OF32><<<g.grid, kBlock, 0, s>>>(p, g.per);
+        k_segment_fixup<T, MAXA, OF32><<<g.grid, kBlock, 0, s>>>(p, g);
     }
     PYG_LAUNCH_CHECK();
     return PYG_OK;
