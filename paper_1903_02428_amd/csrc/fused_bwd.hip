@@ -43,7 +43,6 @@ struct FusedParams {
     RowWalk walk;
     int64_t zero_items, zero_rows;
     int lg;  // log2 of the lanes per slot
-    bool batched;  // sums of slots in three levels (below)
     int64_t F;
     const int32_t *col;
     const int64_t *perm;  // edge id of every slot
@@ -60,7 +59,7 @@ struct FusedParams {
     float *part;          // [2 * nchunks, F]
 };
 
-template <typename TG, typename T, int KIND, int U>
+template <typename TG, typename T, int KIND, int U, bool BATCHED>
 struct FusedBackward {
     using LN = Lane<TG, true>;
     using R = typename LN::R;
@@ -174,11 +173,13 @@ struct FusedBackward {
         // Where the segment kernel sums in narrow windows, a row's chains there
         // are an eighth of its slots; over whole rows of 64 lanes they would be
         // all of them (20,000 rows of 150 slots, F = 256: 1.8e-7 against 8.8e-8
-        // from 64 bits; 9.4e-8 as below). There the slots in flight, then the 64 of a batch, are
-        // summed by themselves before they join the row.
-        float in_batch[EP], in_row[EP];
+        // from 64 bits; 9.4e-8 as below). There (BATCHED) the slots in flight, then
+        // the 64 of a batch, are summed by themselves before they join the row. Registers: a flag read at run time took two wavefronts per SIMD
+        // from the kernels that are never batched.
+        constexpr int NB = BATCHED ? EP : 1;
+        float in_batch[NB], in_row[NB];
 #pragma unroll
-        for (int e = 0; e < EP; ++e) in_batch[e] = in_row[e] = 0.f;
+        for (int e = 0; e < NB; ++e) in_batch[e] = in_row[e] = 0.f;
         int nc = 0, ni = 0;
         float nw = 0.f, nd = 1.f;
         if (s + lane < t) fetch(s + lane, nc, nw, ni, nd);
@@ -203,15 +204,17 @@ struct FusedBackward {
                     if constexpr (MEAN) dd[u] = __shfl(md, idx & (kWave - 1), kWave);
                 }
                 take(jj, ok, ww, ee, dd);
-                if (p.batched)
+                if constexpr (BATCHED) {
+                    const bool flush = st + S * U >= n;
 #pragma unroll
-                    for (int e = 0; e < EP; ++e) in_batch[e] += acc[e], acc[e] = 0.f;
+                    for (int e = 0; e < EP; ++e) {
+                        in_batch[e] += acc[e], acc[e] = 0.f;
+                        if (flush) in_row[e] += in_batch[e], in_batch[e] = 0.f;
+                    }
+                }
             }
-            if (p.batched)
-#pragma unroll
-                for (int e = 0; e < EP; ++e) in_row[e] += in_batch[e], in_batch[e] = 0.f;
         }
-        if (p.batched)
+        if constexpr (BATCHED)
 #pragma unroll
             for (int e = 0; e < EP; ++e) acc[e] = in_row[e];
         for (int off = L; off < kWave; off <<= 1)
@@ -242,7 +245,7 @@ struct FusedBackward {
     }
 };
 
-template <typename TG, typename T, int KIND, int U, bool LIGHT>
+template <typename TG, typename T, int KIND, int U, bool LIGHT, bool BATCHED>
 __global__ __launch_bounds__(kBlock) void k_fused_backward(FusedParams p) {
     const int lane = threadIdx.x & (kWave - 1);
     int64_t c = uniform64((int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave);
@@ -254,7 +257,7 @@ __global__ __launch_bounds__(kBlock) void k_fused_backward(FusedParams p) {
     }
     c -= p.zero_items;
     if (c >= p.walk.nchunks) return;
-    FusedBackward<TG, T, KIND, U> op(p, lane);
+    FusedBackward<TG, T, KIND, U, BATCHED> op(p, lane);
     if constexpr (LIGHT) walk_light(p.walk, c, lane, p.lg, op);
     else walk_heavy(p.walk, c, lane, op);
 }
@@ -280,27 +283,35 @@ FusedWs carve_fused(void *base, int64_t N, int64_t F, int64_t E, int64_t chunk) 
 }
 
 template <typename TG, typename T, int KIND>
-int launch_fused(const FusedParams &p, hipStream_t s) {
-    constexpr int U = KIND == kWeight || KIND == kWeightMean ? 4 : 2;  // slots in flight per lane: registers, and with them wavefronts, count for more
+int launch_fused(const FusedParams &p, bool batched, hipStream_t s) {
+    // slots in flight per lane: registers, and with them wavefronts, count for more
+    constexpr int U = KIND == kWeight || KIND == kWeightMean ? 4 : 2;
     const unsigned grid = static_cast<unsigned>((p.zero_items + p.walk.nchunks + 3) / 4);
-    if (p.lg < 6 && p.walk.E <= kLightMaxDegree * p.walk.N)
-        k_fused_backward<TG, T, KIND, U, true><<<grid, kBlock, 0, s>>>(p);
-    else
-        k_fused_backward<TG, T, KIND, U, false><<<grid, kBlock, 0, s>>>(p);
+    const bool light = p.lg < 6 && p.walk.E <= kLightMaxDegree * p.walk.N;
+    if constexpr (KIND != kRelu && KIND != kMul) {  // the segment kernel's windows take no other
+        if (batched) {
+            if (light) k_fused_backward<TG, T, KIND, U, true, true><<<grid, kBlock, 0, s>>>(p);
+            else k_fused_backward<TG, T, KIND, U, false, true><<<grid, kBlock, 0, s>>>(p);
+            PYG_LAUNCH_CHECK();
+            return PYG_OK;
+        }
+    }
+    if (light) k_fused_backward<TG, T, KIND, U, true, false><<<grid, kBlock, 0, s>>>(p);
+    else k_fused_backward<TG, T, KIND, U, false, false><<<grid, kBlock, 0, s>>>(p);
     PYG_LAUNCH_CHECK();
     return PYG_OK;
 }
 
 template <typename TG, typename T>
-int launch_kind(const FusedParams &p, int kind, hipStream_t s) {
+int launch_kind(const FusedParams &p, int kind, bool batched, hipStream_t s) {
     if constexpr (sizeof(TG) == sizeof(T)) {
-        if (kind == kWeight) return launch_fused<TG, T, kWeight>(p, s);
+        if (kind == kWeight) return launch_fused<TG, T, kWeight>(p, batched, s);
         if constexpr (sizeof(T) == 4)
-            if (kind == kWeightMean) return launch_fused<TG, T, kWeightMean>(p, s);
+            if (kind == kWeightMean) return launch_fused<TG, T, kWeightMean>(p, batched, s);
     }
-    if (kind == kAdd) return launch_fused<TG, T, kAdd>(p, s);
-    if (kind == kRelu) return launch_fused<TG, T, kRelu>(p, s);
-    return launch_fused<TG, T, kMul>(p, s);
+    if (kind == kAdd) return launch_fused<TG, T, kAdd>(p, batched, s);
+    if (kind == kRelu) return launch_fused<TG, T, kRelu>(p, batched, s);
+    return launch_fused<TG, T, kMul>(p, batched, s);
 }
 
 }  // namespace
@@ -333,7 +344,7 @@ int fused_backward(const FusedBackwardArgs &a, void *ws, size_t ws_bytes, hipStr
     p.zero_items = (a.N + p.zero_rows - 1) / p.zero_rows;
     const int64_t ep = a.g_dtype == PYG_BF16 ? 8 : 4, row_bytes = a.F * (16 / ep);
     while ((int64_t(1) << p.lg) < a.F / ep) ++p.lg;
-    p.batched = (a.msg == PYG_MSG_SRC || a.msg == PYG_MSG_EDGE_ADD) && segment_windows(a.N, row_bytes);
+    const bool batched = (a.msg == PYG_MSG_SRC || a.msg == PYG_MSG_EDGE_ADD) && segment_windows(a.N, row_bytes);
     p.F = a.F;
     p.col = a.col, p.perm = a.perm, p.w = a.weight;
     p.g = a.g, p.x = a.x, p.ea = a.edge_attr;
@@ -347,9 +358,9 @@ int fused_backward(const FusedBackwardArgs &a, void *ws, size_t ws_bytes, hipStr
     const int kind = a.msg == PYG_MSG_EDGE_ADD ? kAdd : a.msg == PYG_MSG_EDGE_RELU ? kRelu
                      : a.msg == PYG_MSG_EDGE_MUL ? kMul : a.deg_ptr ? kWeightMean : kWeight;
     p.deg_ptr = a.deg_ptr;
-    if (a.g_dtype == PYG_BF16) PYG_TRY((launch_kind<uint16_t, uint16_t>(p, kind, s)));
-    else if (a.dtype == PYG_BF16) PYG_TRY((launch_kind<float, uint16_t>(p, kind, s)));
-    else PYG_TRY((launch_kind<float, float>(p, kind, s)));
+    if (a.g_dtype == PYG_BF16) PYG_TRY((launch_kind<uint16_t, uint16_t>(p, kind, batched, s)));
+    else if (a.dtype == PYG_BF16) PYG_TRY((launch_kind<float, uint16_t>(p, kind, batched, s)));
+    else PYG_TRY((launch_kind<float, float>(p, kind, batched, s)));
     return segment_fold_pieces(a.rowptr, a.N, a.E, a.F, chunk, w.head_row, w.part, a.grad_x, a.dtype, s);
 }
 
