@@ -173,8 +173,9 @@ struct FusedBackward {
         // Where the segment kernel sums in narrow windows, a row's chains there
         // are an eighth of its slots; over whole rows of 64 lanes they would be
         // all of them (20,000 rows of 150 slots, F = 256: 1.8e-7 against 8.8e-8
-        // from 64 bits; 9.4e-8 as below). There (BATCHED) the slots in flight, then
-        // the 64 of a batch, are summed by themselves before they join the row. Registers: a flag read at run time took two wavefronts per SIMD
+        // from 64 bits). There (BATCHED) the slots in flight, then 32 slots, are
+        // summed by themselves before they join the row (8.8e-8; 9.4e-8 with the 64 of a
+        // batch). Registers: a flag read at run time took two wavefronts per SIMD
         // from the kernels that are never batched.
         constexpr int NB = BATCHED ? EP : 1;
         float in_batch[NB], in_row[NB];
@@ -205,7 +206,7 @@ struct FusedBackward {
                 }
                 take(jj, ok, ww, ee, dd);
                 if constexpr (BATCHED) {
-                    const bool flush = st + S * U >= n;
+                    const bool flush = ((st + S * U) & 31) == 0 || st + S * U >= n;
 #pragma unroll
                     for (int e = 0; e < EP; ++e) {
                         in_batch[e] += acc[e], acc[e] = 0.f;

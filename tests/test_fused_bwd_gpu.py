@@ -64,3 +64,36 @@ def test_edge_one_pass_bits(pyg, case, msg, aggr, dtype):
     px, _ = pyg.propagate_edge_backward(*a, need_grad_edge=False)
     _, pe = pyg.propagate_edge_backward(*a, need_grad_x=False)
     assert torch.equal(gx, px) and torch.equal(ge, pe)
+
+
+@pytest.mark.parametrize("kind,aggr", [("weighted", "sum"), ("weighted", "mean"), ("edge_add", "sum"),
+                                       ("edge_add", "mean")])
+@pytest.mark.parametrize("F", [64, 256])  # 16 lanes a slot (4 side by side) and a whole wavefront
+def test_one_pass_wide_rows_error(pyg, kind, aggr, F):
+    # from 16 MB of rows of whole 128-byte lines on, the segment kernel sums in
+    # windows and the one-pass kernel in three levels: other bits, and no
+    # further from 64 bits (both are rounding noise of 51,200 sums or more: the
+    # 2-norms of two such draws differ by well below 2 %)
+    rng = np.random.default_rng(6200 + F)
+    N, R = (16 << 20) // (4 * F) + 100, 51_200 // F
+    deg = rng.integers(100, 200, R)  # the out-degrees of R sources
+    src, dst = np.repeat(np.arange(R) * 7, deg), rng.integers(0, N, deg.sum())
+    ei = to_dev(np.stack([src, dst]))
+    E = src.size
+    x, g, ea = (to_dev(rng.standard_normal(s).astype(np.float32)) for s in ((N, F), (N, F), (E, F)))
+    w = to_dev(rng.random(E).astype(np.float32)) if kind == "weighted" else None
+    csr, csr_t = pyg.coo_to_csr(ei, N, w, chunk=1024), pyg.coo_to_csr(pyg.reverse_edges(ei), N, w, chunk=1024)
+    if w is not None:
+        one, _ = pyg.propagate_backward(g, x, ei, w, csr, csr_t, aggr, need_grad_w=True)
+        two, _ = pyg.propagate_backward(g, x, ei, w, csr, csr_t, aggr, need_grad_w=True, w_order="csr")
+    else:
+        a = (g, x, ea, csr, kind, aggr, "coo", csr_t)
+        one, _ = pyg.propagate_edge_backward(*a)
+        two, _ = pyg.propagate_edge_backward(*a, need_grad_edge=False)
+    torch.cuda.synchronize()
+    in_deg = np.maximum(np.bincount(dst, minlength=N), 1)[dst] if aggr == "mean" else np.ones(E)
+    coef = (w.cpu().numpy().astype(np.float64) if w is not None else 1.0) / in_deg
+    ref = np.add.reduceat(coef[:, None] * g.cpu().numpy().astype(np.float64)[dst], np.cumsum(deg) - deg)
+    err = [np.linalg.norm(t.cpu().numpy()[np.arange(R) * 7] - ref) / np.linalg.norm(ref) for t in (one, two)]
+    assert not torch.equal(one, two)
+    assert err[0] <= 1.02 * err[1], err
