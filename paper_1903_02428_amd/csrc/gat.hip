@@ -89,7 +89,7 @@ __device__ __forceinline__ typename LN::R load_row(const T *x, int j, int64_t F,
 }
 
 // ------------------------------------------------------------------ forward
-template <typename T, int U, bool GRAD>
+template <typename T, int U, bool GRAD, bool WIDE>
 struct GatForward {
     using LN = Lane<T, true>;
     using R = typename LN::R;
@@ -174,6 +174,16 @@ struct GatForward {
     }
     __device__ __forceinline__ void run(int64_t r, int64_t s, int64_t t, int kind, int64_t slot) {
         begin(r);
+        // WIDE (64 lanes a slot, one sub-group): 32 slots are summed by themselves
+        // before they join the row, whose chain would be a quarter of its slots
+        // (rows of 800 slots, 8 heads of 32, grad a_dst from 64 bits: 7.5e-7 by
+        // the separate kernels, 1.1e-6 in one chain, 5.8e-7 so, at the same
+        // time). Two and more sub-groups are not further off than the separate
+        // kernels, and would lose 1 to 3 % by it.
+        constexpr int NB = WIDE ? EP : 1;
+        float tm = -INFINITY, tz = 0.f, tzp = 0.f, ta[NB], tp[NB];
+#pragma unroll
+        for (int e = 0; e < NB; ++e) ta[e] = tp[e] = 0.f;
         int nx = (s + lane < t) ? column(p, s + lane, hot) : 0;
         for (int64_t base = s; base < t; base += kWave) {
             const int n = static_cast<int>(uniform64((t - base) < kWave ? (t - base) : kWave));
@@ -189,7 +199,24 @@ struct GatForward {
                     jj[u] = __shfl(my, idx & (kWave - 1), kWave);
                 }
                 take(jj, ok);
+                if constexpr (WIDE) {
+                    if (((st + S * U) & 31) != 0 && st + S * U < n) continue;
+                    const float k = pexp(tm, m);
+                    tm = m;
+                    tz = fmaf(tz, k, z), z = 0.f;
+                    tzp = fmaf(tzp, k, zp), zp = 0.f;
+#pragma unroll
+                    for (int e = 0; e < EP; ++e) {
+                        ta[e] = fmaf(ta[e], k, all[e]), all[e] = 0.f;
+                        if constexpr (GRAD) tp[e] = fmaf(tp[e], k, plus[e]), plus[e] = 0.f;
+                    }
+                }
             }
+        }
+        if constexpr (WIDE) {
+            z = tz, zp = tzp;
+#pragma unroll
+            for (int e = 0; e < EP; ++e) all[e] = ta[e], plus[e] = tp[e];
         }
         if (L < kWave) {  // the sub-groups' states: common maximum, then sums
             float mt = m;
@@ -235,7 +262,7 @@ struct GatForward {
     }
 };
 
-template <typename T, int U, bool GRAD, bool LIGHT>
+template <typename T, int U, bool GRAD, bool LIGHT, bool WIDE>
 __global__ __launch_bounds__(kBlock) void k_gat_forward(GatParams p) {
     const int lane = threadIdx.x & (kWave - 1);
     int64_t c = uniform64((int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave);
@@ -254,7 +281,7 @@ __global__ __launch_bounds__(kBlock) void k_gat_forward(GatParams p) {
     const int64_t win = c / p.walk.nchunks;
     if (win >= p.nwin) return;
     c -= win * p.walk.nchunks;
-    GatForward<T, U, GRAD> op(p, lane, win);
+    GatForward<T, U, GRAD, WIDE> op(p, lane, win);
     if constexpr (LIGHT) walk_light(p.walk, c, lane, p.lg, op);
     else walk_heavy(p.walk, c, lane, op);
 }
@@ -699,8 +726,9 @@ int launch_forward(const GatParams &p, hipStream_t s) {
     const int64_t items = p.zero_items + p.walk.nchunks * p.nwin;
     const unsigned grid = static_cast<unsigned>((items + 3) / 4);
     const bool light = p.lg < 6 && p.walk.E <= kLightMaxDegree * p.walk.N;
-    if (light) k_gat_forward<T, U, GRAD, true><<<grid, kBlock, 0, s>>>(p);
-    else k_gat_forward<T, U, GRAD, false><<<grid, kBlock, 0, s>>>(p);
+    if (light) k_gat_forward<T, U, GRAD, true, false><<<grid, kBlock, 0, s>>>(p);
+    else if (p.lg < 6) k_gat_forward<T, U, GRAD, false, false><<<grid, kBlock, 0, s>>>(p);
+    else k_gat_forward<T, U, GRAD, false, true><<<grid, kBlock, 0, s>>>(p);
     PYG_LAUNCH_CHECK();
     if (p.walk.nchunks > 1) {
         const FoldGrid g(p.walk.nchunks, p.F, !fold_split(p.walk.nchunks));
