@@ -432,7 +432,8 @@ __global__ __launch_bounds__(kBlock) void k_gat_node(const T *__restrict__ g, co
             const int64_t nh = k >> lgc;  // node * H + head
             const float4 st = stat[nh];
             tab[nh] = make_float4(st.x, st.y, st.z, d[0]);
-            grad_dst[nh] = (1.f - slope) * (d[1] - d[0] * st.w);
+            // no incoming edges (1 / sum is 0 there alone): an empty sum, whatever g holds
+            grad_dst[nh] = st.z == 0.f ? 0.f : (1.f - slope) * (d[1] - d[0] * st.w);
         }
     }
 }

@@ -172,6 +172,27 @@ def test_gat_fused_takes_what_the_separate_kernels_took(pyg):
         assert torch.allclose(p, q, rtol=1e-5, atol=1e-5)
 
 
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+def test_gat_fused_upstream_of_isolated_nodes(pyg, bad):
+    # a node without incoming edges passes nothing back, whatever its upstream
+    # gradient holds: an empty sum, as by the separate kernels
+    rng = np.random.default_rng(5500)
+    N, H, C = 60, 2, 8
+    ei = synth.random_coo(rng, N, 500)
+    ei[1] %= N // 2  # targets below N / 2
+    x, g = (rng.standard_normal((N, H * C)).astype(np.float32) for _ in range(2))
+    a_src, a_dst = (rng.standard_normal((N, H)).astype(np.float32) for _ in range(2))
+    ref = None
+    for fill in (0.0, bad):
+        g[N // 2:] = fill
+        dev = [to_dev(t).requires_grad_(True) for t in (x, a_src, a_dst)]
+        out = pyg.GATAttention.apply(*dev, pyg.Graph(to_dev(ei), N), 0.2)
+        got = torch.autograd.grad(out, dev, to_dev(g))
+        assert (got[2][N // 2:] == 0).all()
+        ref = ref or got
+        assert all(torch.equal(p, q) for p, q in zip(ref, got))
+
+
 def test_gat_fused_saved_tensor_hooks(pyg):
     # what hooks hand back to the gradient: host copies brought back, unaligned
     # and transposed copies (the same bits), and tensors that no kernel may read
