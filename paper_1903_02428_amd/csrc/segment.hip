@@ -154,9 +154,10 @@ constexpr int kMsgEdgeAdd = 4, kMsgEdgeRelu = 5, kMsgEdgeMul = 6;  // x_j + e, m
 // gradient where x_r + e > 0, x_r being the row's own features (x_self).
 constexpr int kMsgEdgeReluGrad = 7;
 // GCN: the weight of slot p is dinv[col[p]] * w_p * dinv[row] (w_p = 1 without weights)
-constexpr int kMsgGcn = 8;
+constexpr int kMsgGcn = 8, kMsgGcnLen = 9;
+template <int MSG> constexpr bool kGcn = MSG == kMsgGcn || MSG == kMsgGcnLen;
 // messages whose slot carries a scalar weight (read or formed)
-template <int MSG> constexpr bool kWeightedMsg = MSG == 1 || MSG == 8;
+template <int MSG> constexpr bool kWeightedMsg = MSG == kMsgWeighted || kGcn<MSG>;
 
 // The target of row r: r itself, or for a source-blocked virtual row the
 // target it belongs to.
@@ -164,11 +165,14 @@ __device__ __forceinline__ int64_t target_row(const SegParams &p, int64_t r) {
     return p.blocks > 1 ? r % p.rpb : r;
 }
 
-// d^-1/2 of node r: from the array, or (a CSR of unit weights and few edges,
-// where a launch that makes the array costs more) from the row's length by
-// the expression that fills the array.
+// d^-1/2 of node r: from the array, or (kMsgGcnLen: a CSR of unit weights and
+// few edges, where a launch that makes the array costs more) from the row's
+// length by the expression that fills the array. A message of its own: the
+// fp64 root and division as a branch took a wavefront per SIMD (79 -> 82
+// VGPRs) from the kernel that reads the array.
+template <int MSG>
 __device__ __forceinline__ double node_dinv(const SegParams &p, int64_t r) {
-    if (p.dinv) return p.dinv[r];
+    if constexpr (MSG == kMsgGcn) return p.dinv[r];
     const double d = static_cast<double>(p.rowptr[r + 1] - p.rowptr[r]);
     return d > 0.0 ? 1.0 / sqrt(d) : 0.0;
 }
@@ -220,7 +224,7 @@ __device__ __forceinline__ void reduce_piece(const SegParams &p, int64_t r, int6
     }
     // GCN: the row's own d^-1/2
     double dr = 0.0;
-    if constexpr (MSG == kMsgGcn) dr = node_dinv(p, target_row(p, r));
+    if constexpr (kGcn<MSG>) dr = node_dinv<MSG>(p, target_row(p, r));
     // per-head weights: a lane vector never straddles two heads (C is a multiple of its width)
     int64_t hd[NS];
 #pragma unroll
@@ -234,9 +238,9 @@ __device__ __forceinline__ void reduce_piece(const SegParams &p, int64_t r, int6
             c = static_cast<int>(e);
         } else {
             c = __builtin_nontemporal_load(p.col + e);
-            if constexpr (MSG == kMsgGcn) {
+            if constexpr (kGcn<MSG>) {
                 const double wv = p.w ? static_cast<double>(__builtin_nontemporal_load(p.w + e)) : 1.0;
-                w = static_cast<float>(node_dinv(p, c) * wv * dr);
+                w = static_cast<float>(node_dinv<MSG>(p, c) * wv * dr);
                 if (p.norm_out && p.fbase == 0) p.norm_out[e] = w;  // every slot once, by the first window
             }
             if (hot > 0 && p.node_class[c] < hot) c |= static_cast<int>(0x80000000u);
@@ -416,7 +420,7 @@ __device__ __forceinline__ void light_row(const SegParams &p, int64_t r, int64_t
     if constexpr (MSG == kMsgEdgeReluGrad) xi = act ? LN::load(static_cast<const T *>(p.x_self) + rr * p.F + f0) : LN::zero();
     const int64_t hd = MSG == kMsgHeads ? f0 / p.C : 0;
     double dr = 0.0;
-    if constexpr (MSG == kMsgGcn) dr = node_dinv(p, rr);
+    if constexpr (kGcn<MSG>) dr = node_dinv<MSG>(p, rr);
     for (int64_t base = s; base < t; base += U) {
         int jj[U];
         float ww[U];
@@ -432,7 +436,7 @@ __device__ __forceinline__ void light_row(const SegParams &p, int64_t r, int64_t
                 ww[u] = (ok[u] && act) ? p.alpha[ar * p.H + hd] : 0.f;
             }
         }
-        if constexpr (MSG == kMsgGcn) {
+        if constexpr (kGcn<MSG>) {
             // lane q forms the weights of slots q, q + L, ... and hands them out
             const int L = 1 << p.lg_l;
             for (int k = 0; k * L < U; ++k) {
@@ -440,7 +444,7 @@ __device__ __forceinline__ void light_row(const SegParams &p, int64_t r, int64_t
                 float w = 0.f;
                 if (k * L + q < U && e < t) {
                     const double wv = p.w ? static_cast<double>(p.w[e]) : 1.0;
-                    w = static_cast<float>(node_dinv(p, IDENT ? e : p.col[e]) * wv * dr);
+                    w = static_cast<float>(node_dinv<MSG>(p, IDENT ? e : p.col[e]) * wv * dr);
                     if (p.norm_out && p.fbase == 0) p.norm_out[e] = w;
                 }
 #pragma unroll
@@ -1043,7 +1047,8 @@ int launch_msg(const SegParams &p, int msg, bool ident, int ns, bool light, bool
     if (msg == kMsgDiff) return launch_ns<T, VEC, kMsgDiff, MAXA, false>(p, ns, light, fixup, s);
     if (msg == kMsgWeighted) return launch_ns<T, VEC, kMsgWeighted, MAXA, false>(p, ns, light, fixup, s);
     if constexpr (!MAXA) {
-        if (msg == kMsgGcn) return launch_ns<T, VEC, kMsgGcn, false, false>(p, ns, light, fixup, s);
+        if (msg == kMsgGcn && p.dinv) return launch_ns<T, VEC, kMsgGcn, false, false>(p, ns, light, fixup, s);
+        if (msg == kMsgGcn) return launch_ns<T, VEC, kMsgGcnLen, false, false>(p, ns, light, fixup, s);
     }
     return launch_ns<T, VEC, kMsgSrc, MAXA, false>(p, ns, light, fixup, s);
 }
