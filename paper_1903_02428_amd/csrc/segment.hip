@@ -553,10 +553,20 @@ __device__ __forceinline__ void zero_empty_rows(const SegParams &p, int64_t z, i
 // light_row slots with the rest left to the whole wavefront (kLightMixed). The
 // mixed form pays where chunks are large enough for a sub-group to be stuck
 // in a row while the others wait: from 64 slots on (graphs from 262,144 edges;
-// power law, 2.4M edges 352 -> 237 us). Below, its bookkeeping costs more than
-// it saves (mini-batch of 2,048 graphs, 32-slot chunks: 15.6 us short, 19.9 mixed).
+// power law, 2.4M edges: sum 352 -> 210 us, max 282 -> 239). Below, its
+// bookkeeping costs more than it saves (mini-batch of 2,048 graphs, 32-slot
+// chunks: 15.6 us short, 19.9 mixed). Rows of like length gain nothing by it:
+// sums lose nothing either (2M uniform edges 126 short, 120 mixed), max loses
+// its three more registers' worth of wavefronts (211 short, 220 mixed).
 constexpr int kHeavy = 0, kLightShort = 1, kLightMixed = 2;
 inline bool mixed_rows(const SegParams &p) { return p.chunk >= 64; }
+
+// The lane number, unknown to the compiler to be the one before: what depends on
+// it is formed again instead of being kept in registers across the other kind of rows.
+__device__ __forceinline__ int opaque(int lane) {
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
 
 // One wavefront's work on chunk c (features p.fbase .. p.fbase + p.fcnt).
 template <typename T, bool VEC, int NS, int U, int MSG, bool MAXA, bool IDENT, int LIGHT, bool OF32>
@@ -575,40 +585,22 @@ __device__ __forceinline__ void segment_chunk_work(const SegParams &p, int64_t c
     // empty rows that start at E)
     if constexpr (LIGHT == kLightMixed) {
         const int S = kWave >> p.lg_l;
-        const int sg = lane >> p.lg_l;
-        int64_t rb = rA;
+        int64_t rb = rA, rj = 0;  // the next batch of rows; the batch of the jobs
+        uint64_t jobs = 0;
+        bool more = true;
         while (true) {
-            const int64_t rp = p.rowptr[(rb + lane) < p.n_rows ? (rb + lane) : p.n_rows];
-            // rows rb .. rb+cnt-1 start in the chunk (rows starting at E are
-            // empty: zero-filled separately); lane i+1 holds the end of row rb+i
-            const bool in = lane < kWave - 1 && rb + lane < p.n_rows && rp < (last ? p.E : e1);
-            const int cnt = __popcll(__ballot(in));
-            const int64_t s_first = lane_value64(rp, 0);
-            if (cnt == kWave - 1 && lane_value64(rp, kWave - 1) == s_first) {
-                // 63 empty rows in a row: skip to the last row that starts at s_first
-                rb = uniform_lower_bound(p.rowptr, p.n_rows + 1, s_first + 1) - 1;
-                continue;
-            }
-            for (int i0 = 0; i0 < cnt; i0 += S) {
-                const int i = i0 + sg;
-                const int ii = i < cnt ? i : cnt - 1;
-                const int64_t s = __shfl(rp, ii, kWave), t = __shfl(rp, ii + 1, kWave);
-                light_row<T, VEC, U, MSG, MAXA, IDENT, OF32>(p, rb + i, s, t, i < cnt && t > s && t - s <= p.light_row, lane);
-            }
-            // the whole wavefront: rows above light_row slots (a sub-group would
-            // walk one alone while the others wait), the first piece of a long
-            // row (only the chunk's last row can be one), the piece that came in
-            const int64_t len = __shfl_down(rp, 1, kWave) - rp;
-            uint64_t jobs = __ballot(lane < cnt && len > p.light_row);
+            // the whole wavefront: the piece that came in, then of each batch the
+            // rows above light_row slots (a sub-group would walk one alone while
+            // the others wait) and the first piece of a long row (only the
+            // chunk's last row can be one)
             while (cont || jobs) {
                 int64_t r = rA - 1, s = e0, t = rpA < e1 ? rpA : e1, slot = 2 * c;
                 int kind = kPartial;
                 if (!cont) {
-                    const int k = __ffsll(static_cast<unsigned long long>(jobs)) - 1;
+                    r = rj + __ffsll(static_cast<unsigned long long>(jobs)) - 1;
                     jobs &= jobs - 1;
-                    r = rb + k;
-                    s = lane_value64(rp, k);
-                    t = lane_value64(rp, k + 1);
+                    s = uniform64(p.rowptr[r]);
+                    t = uniform64(p.rowptr[r + 1]);
                     kind = kFull;
                     if (t - s > p.chunk) {
                         kind = kPartial;
@@ -618,9 +610,31 @@ __device__ __forceinline__ void segment_chunk_work(const SegParams &p, int64_t c
                     }
                 }
                 cont = false;
-                reduce_piece<T, VEC, NS, U, MSG, MAXA, IDENT, OF32>(p, r, s, t, kind, slot, lane, 0);
+                reduce_piece<T, VEC, NS, U, MSG, MAXA, IDENT, OF32>(p, r, s, t, kind, slot, opaque(lane), 0);
             }
-            if (cnt < kWave - 1) break;  // the chunk's rows end in this batch
+            if (!more) break;
+            const int ln = opaque(lane), sg = ln >> p.lg_l;
+            const int64_t rp = p.rowptr[(rb + ln) < p.n_rows ? (rb + ln) : p.n_rows];
+            // rows rb .. rb+cnt-1 start in the chunk (rows starting at E are
+            // empty: zero-filled separately); lane i+1 holds the end of row rb+i
+            const bool in = ln < kWave - 1 && rb + ln < p.n_rows && rp < (last ? p.E : e1);
+            const int cnt = __popcll(__ballot(in));
+            const int64_t s_first = lane_value64(rp, 0);
+            if (cnt == kWave - 1 && lane_value64(rp, kWave - 1) == s_first) {
+                // 63 empty rows in a row: skip to the last row that starts at s_first
+                rb = uniform_lower_bound(p.rowptr, p.n_rows + 1, s_first + 1) - 1;
+                continue;
+            }
+            const int64_t len = __shfl_down(rp, 1, kWave) - rp;
+            jobs = __ballot(ln < cnt && len > p.light_row);
+            rj = rb;
+            for (int i0 = 0; i0 < cnt; i0 += S) {
+                const int i = i0 + sg;
+                const int ii = i < cnt ? i : cnt - 1;
+                const int64_t s = __shfl(rp, ii, kWave), t = __shfl(rp, ii + 1, kWave);
+                light_row<T, VEC, U, MSG, MAXA, IDENT, OF32>(p, rb + i, s, t, i < cnt && t > s && t - s <= p.light_row, ln);
+            }
+            more = cnt == kWave - 1;  // else the chunk's rows end in this batch
             rb += cnt;
         }
         p.head_row[c] = head;  // uniform: every lane stores the same value (no lane-0 branch)
@@ -693,8 +707,16 @@ __device__ __forceinline__ void segment_chunk_work(const SegParams &p, int64_t c
     p.head_row[c] = head;  // uniform: every lane stores the same value (no lane-0 branch)
 }
 
+// Wavefronts per SIMD that the compiler has to leave room for. The mixed form
+// holds both kinds of rows; unasked it kept so many scalar registers (106) that
+// a sum of source rows had 7 wavefronts where its 60 vector registers allow 8
+// (2M uniform edges, F = 64: 134.6 us so, 119.7 with 8). Kernels that use more
+// vector registers lose by such a bound (max: 220 us without, 239 with 7).
+template <int MSG, bool MAXA, int LIGHT>
+constexpr int kMinWaves = LIGHT == kLightMixed && MSG == kMsgSrc && !MAXA ? 8 : 1;
+
 template <typename T, bool VEC, int NS, int U, int MSG, bool MAXA, bool IDENT, int LIGHT, bool OF32 = false>
-__global__ __launch_bounds__(kBlock) void k_segment(SegParams p) {
+__global__ __launch_bounds__(kBlock, (kMinWaves<MSG, MAXA, LIGHT>)) void k_segment(SegParams p) {
     const int lane = threadIdx.x & (kWave - 1);
     int64_t c = uniform64((int64_t)blockIdx.x * (kBlock / kWave) + (threadIdx.x / kWave));
     if (c < p.zero_items) {  // the first work items: empty rows (short, dispatched first)
