@@ -288,8 +288,14 @@ extern "C" int pyg_gcn_propagate(const void *x, int dtype, int64_t N, int64_t F,
     void *seg_ws = reinterpret_cast<char *>(norm_ws) + align_up(static_cast<size_t>(E) * 4, 256);
     // unit weights and few edges: the propagate takes d^-1/2 from the row
     // lengths itself (a square root per slot, spread over the lanes, against a
-    // launch: a 13k-edge graph 16.4 -> 11.8 us; from 2^20 slots on they outweigh it)
-    const bool lengths = !csr->weight && E <= (int64_t(1) << 20);
+    // launch: a 13k-edge graph 16.4 -> 11.8 us; from 2^20 slots on they outweigh
+    // it). Rows that take a whole wavefront (long ones, or more than 32 single
+    // features) pay one for all 64 lanes and a second for the row: up to 2^17
+    // slots (F = 33: 100k edges 23.4 -> 20.7 us, 200k the same, 500k 61 -> 63,
+    // 1M 119 -> 129; 1M edges in rows of 50, F = 64: 44.2 -> 45.0).
+    const int64_t sz = dtype == PYG_BF16 ? 2 : 4;
+    const bool spread = E <= kLightMaxDegree * N && (F * sz % 16 == 0 || F <= 32);
+    const bool lengths = !csr->weight && E <= (int64_t(1) << (spread ? 20 : 17));
     if (csr->weight)
         k_row_dinv_weighted<<<grid_for(N, kBlock / kWave, 1 << 16), kBlock, 0, s>>>(csr->rowptr, csr->weight, N, dinv);
     else if (!lengths)

@@ -168,3 +168,16 @@ def test_gcn_propagate_blocked_degree_from_blocks(pyg, N, E, F, weighted):
     out2 = pyg.gcn_propagate_blocked(to_dev(x_np), None, bc)
     torch.cuda.synchronize()
     check_sum(out2, ref, sabs, False, f"gcn_propagate_blocked (d from blocks, no norms) N={N} E={E} F={F}")
+
+
+@pytest.mark.parametrize("N,E,F", [(20000, 1 << 17, 33), (20000, (1 << 17) + 1, 33), (3000, 1 << 17, 64),
+                                   (3000, (1 << 17) + 1, 64), (90000, 1 << 20, 4), (90000, (1 << 20) + 1, 4)])
+def test_gcn_propagate_unit_weights_around_the_lengths_limit(pyg, N, E, F):
+    # d^-1/2 from the row lengths up to these edge counts, from an array above:
+    # the bits of weights that are all one
+    rng = np.random.default_rng(9600 + E + F)
+    ei = to_dev(synth.random_coo(rng, N, E))
+    x = to_dev(rng.standard_normal((N, F)).astype(np.float32))
+    unit = pyg.coo_to_csr(ei, N)
+    ones = pyg.coo_to_csr(ei, N, torch.ones(E, device="cuda"))
+    assert torch.equal(pyg.gcn_propagate(x, unit), pyg.gcn_propagate(x, ones))
