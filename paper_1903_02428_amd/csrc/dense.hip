@@ -360,11 +360,15 @@ template <typename TO, int NU, int WC, int KC>
 int launch_dense_f32(const float *x, int64_t N, int64_t Fi, const float *theta, int64_t Fo, TO *out, bool vec,
                      hipStream_t s) {
     constexpr int64_t rows = 16 * (kBlock / kWave / WC), cols = 16 * NU * WC;
-    const dim3 grid(static_cast<unsigned>((N + rows - 1) / rows), static_cast<unsigned>((Fo + cols - 1) / cols));
+    constexpr int64_t most = (int64_t(1) << 23) * rows;  // rows of a launch: it is below 2^32 threads
     const bool tvec = Fo % 4 == 0 && (reinterpret_cast<uintptr_t>(theta) & 15) == 0;
-    if (vec) k_dense_f32<TO, true, NU, WC, KC><<<grid, kBlock, 0, s>>>(x, N, Fi, theta, Fo, tvec, out);
-    else k_dense_f32<TO, false, NU, WC, KC><<<grid, kBlock, 0, s>>>(x, N, Fi, theta, Fo, tvec, out);
-    PYG_LAUNCH_CHECK();
+    for (int64_t n0 = 0; n0 < N; n0 += most, x += most * Fi, out += most * Fo) {
+        const int64_t n = N - n0 < most ? N - n0 : most;
+        const dim3 grid(static_cast<unsigned>((n + rows - 1) / rows), static_cast<unsigned>((Fo + cols - 1) / cols));
+        if (vec) k_dense_f32<TO, true, NU, WC, KC><<<grid, kBlock, 0, s>>>(x, n, Fi, theta, Fo, tvec, out);
+        else k_dense_f32<TO, false, NU, WC, KC><<<grid, kBlock, 0, s>>>(x, n, Fi, theta, Fo, tvec, out);
+        PYG_LAUNCH_CHECK();
+    }
     return PYG_OK;
 }
 

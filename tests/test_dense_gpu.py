@@ -153,3 +153,12 @@ def test_dense_transform_out_over_theta(pyg, dtype, shape):
     theta.copy_(t)
     pyg.dense_transform(x, theta, dtype, out=out)
     assert torch.equal(out, ref)
+
+
+def test_dense_f32_more_rows_than_a_launch():
+    # 2^24 workgroups of 64 rows are 2^32 threads: the rows go out in several launches
+    import paper_1903_02428_amd as pyg
+    N = (1 << 30) + 33
+    x = torch.arange(N, dtype=torch.int32, device="cuda").to(torch.float32).view(N, 1)
+    out = pyg.dense_transform(x, torch.full((1, 1), 3.0, device="cuda"), out_dtype=torch.float32)
+    assert torch.equal(out, x * 3.0)
