@@ -237,10 +237,24 @@ __global__ __launch_bounds__(kBlock) void k_dense(const uint16_t *__restrict__ x
 #ifndef PYG_DENSE_F32_PERSIST
 #define PYG_DENSE_F32_PERSIST 2
 #endif
+// Rows from which a wavefront takes two row tiles (33 to 64 columns: 4M x 16 ->
+// 33 370 -> 356 us, 1M x 500 -> 64 798 -> 731; with 128 columns it loses, 734 ->
+// 774), and from which rows of no whole vectors are loaded by one wavefront
+// instead of two side by side (1M x 257 -> 130 2022 -> 1625 us).
+// Elements of X from which Theta's rows of no whole vectors are padded by a
+// launch of 2.7 us first, instead of loaded singly by every workgroup (20k x 500
+// -> 33 28.8 -> 26.8 us, 100k x 300 -> 33 68.9 -> 60.5, 1M x 256 -> 129 1956 ->
+// 1500; 5k x 500 -> 33 14.5 without, 17.5 padded, 100k x 64 -> 10 9.1 and 11.8).
+constexpr int64_t kPadElements = int64_t(8) << 20;
+constexpr int64_t kTallRows = 200000, kRaggedRows = 50000;
 
-__global__ void k_theta_copy(const float *__restrict__ theta, int64_t n, float *__restrict__ copy) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        copy[i] = theta[i];
+// Theta with rows of ld >= Fo floats, zeros past Fo.
+__global__ void k_theta_copy(const float *__restrict__ theta, int64_t Fi, int64_t Fo, int64_t ld, float *__restrict__ copy) {
+    const int64_t n = Fi * ld;
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t k = i / ld, c = i - k * ld;
+        copy[i] = c < Fo ? theta[k * Fo + c] : 0.f;
+    }
 }
 
 __global__ void k_theta_t_f32(const float *__restrict__ theta, int64_t Fi, int64_t Fo, int64_t Kp, int64_t Fo_pad,
@@ -268,8 +282,8 @@ __device__ __forceinline__ f32x4 load_af(const float *__restrict__ x, int64_t N,
     }
 }
 
-// A workgroup owns 16 * 4 / WC rows and 16 * NU * WC columns: WC wavefronts
-// side by side, each 16 rows by NU tiles of 16 columns, so that no tile of a
+// A workgroup owns 16 * RT * 4 / WC rows and 16 * NU * WC columns: WC wavefronts
+// side by side, each RT * 16 rows by NU tiles of 16 columns, so that no tile of a
 // narrow Theta is padding and a graph of 20k nodes still gives every SIMD a
 // few wavefronts (rows of 32 and 128-column tiles gave it 0.6, and half of
 // the tiles were padding for 64 columns). Theta is staged as it lies, KC rows
@@ -278,10 +292,10 @@ __device__ __forceinline__ f32x4 load_af(const float *__restrict__ x, int64_t N,
 // Theta loaded before this one is multiplied. 19,717 x 500 -> 64: 57 + 5 us
 // (the transposing launch) before, 25 us now; the matrix cores alone need 8 us
 // at the fp32 rate, X and the output 9 us.
-template <typename TO, bool VEC, int NU, int WC, int KC>
+template <typename TO, bool VEC, int RT, int NU, int WC, int KC>
 __global__ __launch_bounds__(kBlock) void k_dense_f32(const float *__restrict__ x, int64_t N, int64_t Fi,
-                                                      const float *__restrict__ theta, int64_t Fo, bool tvec,
-                                                      TO *__restrict__ out) {
+                                                      const float *__restrict__ theta, int64_t ld, int64_t Fo,
+                                                      bool tvec, TO *__restrict__ out) {
     constexpr int WR = kBlock / kWave / WC, COLS = 16 * NU * WC, CS = COLS + 4;
     constexpr int SA = KC / 16;                    // 16-k steps of a stage
     constexpr int SB = KC * COLS / 4 / kBlock;     // 16-byte pieces of Theta per thread and stage
@@ -289,14 +303,16 @@ __global__ __launch_bounds__(kBlock) void k_dense_f32(const float *__restrict__ 
     __shared__ __align__(16) float lds[2][KC * CS];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
-    const int64_t row = ((int64_t)blockIdx.x * WR + wave / WC) * 16 + (lane & 15);
+    const int64_t row = ((int64_t)blockIdx.x * WR + wave / WC) * (16 * RT) + (lane & 15);  // and every 16th, RT of them
     const int64_t c0 = (int64_t)blockIdx.y * COLS;
     const int cw = (wave % WC) * (16 * NU);
     const int li = lane & 15, lg = lane >> 4;
 
-    auto load_x = [&](int64_t kc, f32x4 (&a)[SA]) {
+    auto load_x = [&](int64_t kc, f32x4 (&a)[RT][SA]) {
 #pragma unroll
-        for (int st = 0; st < SA; ++st) a[st] = load_af<VEC>(x, N, Fi, row, kc + 16 * st + 4 * lg);
+        for (int t = 0; t < RT; ++t)
+#pragma unroll
+            for (int st = 0; st < SA; ++st) a[t][st] = load_af<VEC>(x, N, Fi, row + 16 * t, kc + 16 * st + 4 * lg);
     };
     auto load_theta = [&](int64_t kc, f32x4 (&b)[SB]) {
 #pragma unroll
@@ -305,8 +321,8 @@ __global__ __launch_bounds__(kBlock) void k_dense_f32(const float *__restrict__ 
             const int64_t k = kc + q / (COLS / 4), c = c0 + 4 * (q % (COLS / 4));
             f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
             if (k < Fi) {
-                const float *t = theta + k * Fo + c;
-                if (tvec && c + 4 <= Fo) {
+                const float *t = theta + k * ld + c;
+                if (tvec && c + 4 <= ld) {
                     v = *reinterpret_cast<const f32x4 *>(t);
                 } else {
 #pragma unroll
@@ -316,10 +332,12 @@ __global__ __launch_bounds__(kBlock) void k_dense_f32(const float *__restrict__ 
             b[i] = v;
         }
     };
-    f32x4 acc[NU];
+    f32x4 acc[RT][NU];
 #pragma unroll
-    for (int u = 0; u < NU; ++u) acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-    f32x4 a[SA], an[SA], b[SB];
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int u = 0; u < NU; ++u) acc[t][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 a[RT][SA], an[RT][SA], b[SB];
     load_x(0, a);
     load_theta(0, b);
     int buf = 0;
@@ -343,30 +361,40 @@ __global__ __launch_bounds__(kBlock) void k_dense_f32(const float *__restrict__ 
             for (int e = 0; e < 4; ++e) {
                 const float *t = &lds[buf][(16 * st + 4 * lg + e) * CS + cw + li];
 #pragma unroll
-                for (int u = 0; u < NU; ++u)
-                    acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(t[16 * u], a[st][e], acc[u], 0, 0, 0);
+                for (int u = 0; u < NU; ++u) {
+                    const float bv = t[16 * u];
+#pragma unroll
+                    for (int r = 0; r < RT; ++r)
+                        acc[r][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(bv, a[r][st][e], acc[r][u], 0, 0, 0);
+                }
             }
         }
 #pragma unroll
-        for (int st = 0; st < SA; ++st) a[st] = an[st];
+        for (int t = 0; t < RT; ++t)
+#pragma unroll
+            for (int st = 0; st < SA; ++st) a[t][st] = an[t][st];
     }
-    if (row >= N) return;
     const bool vec = Fo % 4 == 0 && (reinterpret_cast<uintptr_t>(out) & (4 * sizeof(TO) - 1)) == 0;
 #pragma unroll
-    for (int u = 0; u < NU; ++u) store4(out, row, c0 + cw + 16 * u + 4 * lg, Fo, acc[u], vec);
+    for (int t = 0; t < RT; ++t) {
+        if (row + 16 * t >= N) return;
+#pragma unroll
+        for (int u = 0; u < NU; ++u) store4(out, row + 16 * t, c0 + cw + 16 * u + 4 * lg, Fo, acc[t][u], vec);
+    }
 }
 
-template <typename TO, int NU, int WC, int KC>
-int launch_dense_f32(const float *x, int64_t N, int64_t Fi, const float *theta, int64_t Fo, TO *out, bool vec,
-                     hipStream_t s) {
-    constexpr int64_t rows = 16 * (kBlock / kWave / WC), cols = 16 * NU * WC;
+// theta has rows of ld floats (Fo, or more with zeros between).
+template <typename TO, int RT, int NU, int WC, int KC>
+int launch_dense_f32(const float *x, int64_t N, int64_t Fi, const float *theta, int64_t ld, int64_t Fo, TO *out,
+                     bool vec, hipStream_t s) {
+    constexpr int64_t rows = 16 * RT * (kBlock / kWave / WC), cols = 16 * NU * WC;
     constexpr int64_t most = (int64_t(1) << 23) * rows;  // rows of a launch: it is below 2^32 threads
-    const bool tvec = Fo % 4 == 0 && (reinterpret_cast<uintptr_t>(theta) & 15) == 0;
+    const bool tvec = ld % 4 == 0 && (reinterpret_cast<uintptr_t>(theta) & 15) == 0;
     for (int64_t n0 = 0; n0 < N; n0 += most, x += most * Fi, out += most * Fo) {
         const int64_t n = N - n0 < most ? N - n0 : most;
         const dim3 grid(static_cast<unsigned>((n + rows - 1) / rows), static_cast<unsigned>((Fo + cols - 1) / cols));
-        if (vec) k_dense_f32<TO, true, NU, WC, KC><<<grid, kBlock, 0, s>>>(x, n, Fi, theta, Fo, tvec, out);
-        else k_dense_f32<TO, false, NU, WC, KC><<<grid, kBlock, 0, s>>>(x, n, Fi, theta, Fo, tvec, out);
+        if (vec) k_dense_f32<TO, true, RT, NU, WC, KC><<<grid, kBlock, 0, s>>>(x, n, Fi, theta, ld, Fo, tvec, out);
+        else k_dense_f32<TO, false, RT, NU, WC, KC><<<grid, kBlock, 0, s>>>(x, n, Fi, theta, ld, Fo, tvec, out);
         PYG_LAUNCH_CHECK();
     }
     return PYG_OK;
@@ -374,11 +402,14 @@ int launch_dense_f32(const float *x, int64_t N, int64_t Fi, const float *theta, 
 
 // Columns of a workgroup: as few as hold Theta's, up to 128.
 template <typename TO>
-int dense_f32(const float *x, int64_t N, int64_t Fi, const float *theta, int64_t Fo, TO *out, bool vec, hipStream_t s) {
-    if (Fo <= 16) return launch_dense_f32<TO, 1, 1, 64>(x, N, Fi, theta, Fo, out, vec, s);
-    if (Fo <= 32) return launch_dense_f32<TO, 2, 1, 64>(x, N, Fi, theta, Fo, out, vec, s);
-    if (Fo <= 64) return launch_dense_f32<TO, 2, 2, 64>(x, N, Fi, theta, Fo, out, vec, s);
-    return launch_dense_f32<TO, 4, 2, 32>(x, N, Fi, theta, Fo, out, vec, s);
+int dense_f32(const float *x, int64_t N, int64_t Fi, const float *theta, int64_t ld, int64_t Fo, TO *out, bool vec,
+              hipStream_t s) {
+    if (Fo <= 16) return launch_dense_f32<TO, 1, 1, 1, 64>(x, N, Fi, theta, ld, Fo, out, vec, s);
+    if (Fo <= 32) return launch_dense_f32<TO, 1, 2, 1, 64>(x, N, Fi, theta, ld, Fo, out, vec, s);
+    if (Fo <= 64 && N >= kTallRows) return launch_dense_f32<TO, 2, 2, 2, 64>(x, N, Fi, theta, ld, Fo, out, vec, s);
+    if (Fo <= 64) return launch_dense_f32<TO, 1, 2, 2, 64>(x, N, Fi, theta, ld, Fo, out, vec, s);
+    if (!vec && N >= kRaggedRows) return launch_dense_f32<TO, 1, 8, 1, 32>(x, N, Fi, theta, ld, Fo, out, vec, s);
+    return launch_dense_f32<TO, 1, 4, 2, 32>(x, N, Fi, theta, ld, Fo, out, vec, s);
 }
 
 // Fi <= 128: persistent workgroups that stage the whole Theta^T (128 columns
@@ -486,18 +517,23 @@ extern "C" int pyg_dense_transform(const void *x, int x_dtype, int64_t N, int64_
         const bool vec = Fi % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0;
         const float *xf = static_cast<const float *>(x), *th = static_cast<const float *>(theta);
         const int64_t nblocks = (N + kRowsWave * (kBlock / kWave) - 1) / (kRowsWave * (kBlock / kWave));
-        // out over Theta's memory: the product reads a copy (ws holds Fi * Fo floats)
+        // Theta as it lies, but for: out over its memory, and rows of no whole
+        // 16-byte vectors of a large product
         const char *tb = static_cast<const char *>(theta);
-        if (ob < tb + Fi * Fo * xsz && tb < ob + N * Fo * osz) {
+        const bool over = ob < tb + Fi * Fo * xsz && tb < ob + N * Fo * osz;
+        const bool ragged = (Fo % 4 != 0 || (reinterpret_cast<uintptr_t>(theta) & 15) != 0) && N * Fi >= kPadElements;
+        const bool persist = Fi <= 128 && Fo > 64 && nblocks >= PYG_DENSE_F32_PERSIST * kPersistBlocksF;
+        int64_t ld = Fo;
+        if (over || (ragged && !persist)) {  // the workspace holds Fi rows of Fo rounded up to 16
             float *copy = static_cast<float *>(ws);
-            k_theta_copy<<<grid_for(Fi * Fo, kBlock * 4), kBlock, 0, s>>>(th, Fi * Fo, copy);
+            ld = (Fo + 3) / 4 * 4;
+            k_theta_copy<<<grid_for(Fi * ld, kBlock * 4), kBlock, 0, s>>>(th, Fi, Fo, ld, copy);
             PYG_LAUNCH_CHECK();
-            return out_dtype == PYG_F32 ? dense_f32(xf, N, Fi, copy, Fo, static_cast<float *>(out), vec, s)
-                                        : dense_f32(xf, N, Fi, copy, Fo, static_cast<uint16_t *>(out), vec, s);
+            th = copy;
         }
         // persistent workgroups with the whole Theta^T staged once: K of one
         // stage, columns for its 128-column tiles and two rounds of row blocks
-        if (Fi <= 128 && Fo > 64 && nblocks >= PYG_DENSE_F32_PERSIST * kPersistBlocksF) {
+        if (persist && !over) {
             const int64_t Kp = kpadf(Fi), Fp = fopad(Fo);
             float *tt = static_cast<float *>(ws);
             k_theta_t_f32<<<grid_for(Fp * Kp, kBlock * 4), kBlock, 0, s>>>(th, Fi, Fo, Kp, Fp, tt);
@@ -515,8 +551,8 @@ extern "C" int pyg_dense_transform(const void *x, int x_dtype, int64_t N, int64_
             PYG_LAUNCH_CHECK();
             return PYG_OK;
         }
-        return out_dtype == PYG_F32 ? dense_f32(xf, N, Fi, th, Fo, static_cast<float *>(out), vec, s)
-                                    : dense_f32(xf, N, Fi, th, Fo, static_cast<uint16_t *>(out), vec, s);
+        return out_dtype == PYG_F32 ? dense_f32(xf, N, Fi, th, ld, Fo, static_cast<float *>(out), vec, s)
+                                    : dense_f32(xf, N, Fi, th, ld, Fo, static_cast<uint16_t *>(out), vec, s);
     }
     const int64_t Kp = kpad(Fi), Fp = fopad(Fo);
     uint16_t *tt = static_cast<uint16_t *>(ws);

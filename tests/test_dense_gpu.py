@@ -155,6 +155,27 @@ def test_dense_transform_out_over_theta(pyg, dtype, shape):
     assert torch.equal(out, ref)
 
 
+# fp32 operands at row counts that take the other tiles: the persistent
+# workgroups (Fi <= 128, Fo > 64, from 131,072 rows on), two row tiles per
+# wavefront (32 < Fo <= 64, from 200,000 on), 128 columns per wavefront (rows of
+# no whole vectors, from 50,000 on); ragged K, columns and last rows
+@pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("N,Fi,Fo", [(131_100, 66, 130), (131_100, 40, 100), (131_100, 128, 129), (131_100, 100, 256),
+                                     (200_007, 16, 33), (200_007, 67, 63), (200_007, 130, 64), (50_005, 66, 130),
+                                     (50_005, 131, 65), (50_005, 301, 256), (50_005, 68, 129)])
+def test_dense_f32_tall(N, Fi, Fo, out_dtype):
+    import paper_1903_02428_amd as pyg
+    rng = np.random.default_rng(9900 + N + Fi + Fo)
+    x = rng.standard_normal((N, Fi)).astype(np.float32)
+    theta = (rng.standard_normal((Fi, Fo)) / np.sqrt(Fi)).astype(np.float32)
+    out = pyg.dense_transform(to_dev(x), to_dev(theta), out_dtype=out_dtype)
+    torch.cuda.synchronize()
+    rows = np.unique(np.concatenate([np.arange(300), rng.integers(0, N, 2000), np.arange(N - 300, N)]))
+    ref = x[rows].astype(np.float64) @ theta.astype(np.float64)
+    mag = np.abs(x[rows]).astype(np.float64) @ np.abs(theta).astype(np.float64)
+    check_sum(out[to_dev(rows)], ref, mag, out_dtype == torch.bfloat16, f"tall N={N} Fi={Fi} Fo={Fo}")
+
+
 def test_dense_f32_more_rows_than_a_launch():
     # 2^24 workgroups of 64 rows are 2^32 threads: the rows go out in several launches
     import paper_1903_02428_amd as pyg
