@@ -226,7 +226,9 @@ constexpr int64_t kLightMaxDegree = PYG_LIGHT_MAX_DEGREE;
 // mean, 16 to 32 (power law, 1.6M edges of mean 8: the edge-message kernel
 // 298 us without the limit, 191 at 32, 157 at 16; uniform rows of mean 16: 79 us
 // without, 85 at 32, 111 at 16, which half of them exceed).
-// At most the chunk: longer rows are cut into pieces.
+// At most the chunk: longer rows are cut into pieces. The segment kernel does so
+// from chunks of kMixedChunk slots on.
+constexpr int64_t kMixedChunk = 64;
 static inline int64_t light_row_slots(int64_t E, int64_t n_rows, int64_t chunk) {
     int64_t m = n_rows > 0 ? 2 * E / n_rows : 0;
     m = m < 16 ? 16 : m > 32 ? 32 : m;

@@ -7,12 +7,13 @@
 //   x_j + e         grad x_j += g_i            grad e = g_i
 //   max(x_j + e, 0) both times [x_j + e > 0]
 //   x_j e           grad x_j += e g_i          grad e = g_i x_j
-// (g scaled by 1 / deg_i under mean; scalar weights divide here). Over the rows of the reversed CSR x_j
-// stays in registers, so one gather of g_i serves both; a second pass over the
-// CSR gathered x_j again and, for edge features, read every e again. The
-// per-edge arrays are reached through perm (the edge ids), loaded with the
-// columns one batch of 64 slots ahead. Deterministic: one writer per edge,
-// the segment kernel's order for the sums (the same bits as its whole rows).
+// (g scaled by 1 / deg_i under mean; scalar weights divide here). Over the rows
+// of the reversed CSR x_j stays in registers, so one gather of g_i serves both;
+// a second pass over the CSR gathered x_j again and, for edge features, read
+// every e again. The per-edge arrays are reached through perm (the edge ids),
+// loaded with the columns one batch of 64 slots ahead. Deterministic: one writer
+// per edge, and the segment kernel's order for the sums, hence its bits, but
+// for rows that it sums in windows of 128 bytes.
 //
 // Measured on a power-law graph of 100,000 nodes and 2M edges: both gradients
 // of the weighted sum (fp32, F = 100) 657 us in two passes, 180 us in one; of
@@ -32,8 +33,9 @@ constexpr int kWeight = 0, kAdd = 1, kRelu = 2, kMul = 3;
 // rows scaled beforehand was 1.2 times as far from 64 bits).
 constexpr int kWeightMean = 4;
 
-// n / d, correctly rounded, from inv = 1 / d correctly rounded: one correction of
-// n * inv by its exact remainder; the fix-up settles infinities and NaN.
+// n / d from inv = 1 / d, correctly rounded where the quotient is a normal
+// number (a subnormal one may miss a tie): one correction of n * inv by its exact
+// remainder (Markstein's step); the fix-up settles infinities and NaN.
 __device__ __forceinline__ float div_by(float n, float d, float inv) {
     const float q = n * inv;
     return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-d, q, n), inv, q), d, n);
@@ -97,7 +99,8 @@ struct FusedBackward {
         if constexpr (KIND == kRelu || KIND == kMul) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                if (ok[u] && act) ev[u] = *reinterpret_cast<const Share<T> *>(static_cast<const T *>(p.ea) + (int64_t)ee[u] * p.F + f0);
+                const T *e = static_cast<const T *>(p.ea) + (int64_t)ee[u] * p.F + f0;
+                if (ok[u] && act) ev[u] = *reinterpret_cast<const Share<T> *>(e);
                 else ev[u] = Share<T>{};
             }
         }
@@ -330,8 +333,9 @@ bool fused_backward_ok(const FusedBackwardArgs &a) {
     // (weights: g in the type of x, as the dot products of the pass over the CSR
     // take it; a bf16 mean sums fp32 rows, 4 features a lane: the separate kernels)
     if (a.deg_ptr && a.dtype != PYG_F32) return false;
-    return a.E > 0 && a.F > 0 && (a.msg != PYG_MSG_SRC || a.g_dtype == a.dtype) && a.F % ep == 0 && a.F / ep <= kWave && a.perm && al(a.g, 16) && al(a.x, ep * sz) &&
-           al(a.edge_attr, ep * sz) && al(a.grad_x, ep * sz) && al(a.grad_e, ep * sz);
+    return a.E > 0 && a.F > 0 && (a.msg != PYG_MSG_SRC || a.g_dtype == a.dtype) && a.F % ep == 0 &&
+           a.F / ep <= kWave && a.perm && al(a.g, 16) && al(a.x, ep * sz) && al(a.edge_attr, ep * sz) &&
+           al(a.grad_x, ep * sz) && al(a.grad_e, ep * sz);
 }
 
 int fused_backward(const FusedBackwardArgs &a, void *ws, size_t ws_bytes, hipStream_t s) {
@@ -339,7 +343,10 @@ int fused_backward(const FusedBackwardArgs &a, void *ws, size_t ws_bytes, hipStr
     const FusedWs w = carve_fused(ws, a.N, a.F, a.E, chunk);
     if (!ws || ws_bytes < w.bytes) return PYG_ERR_WORKSPACE;
     FusedParams p{};
-    p.walk = {a.rowptr, a.N, a.E, chunk, light_row_slots(a.E, a.N, chunk), (a.E + chunk - 1) / chunk, w.head_row};
+    // below 64-slot chunks the segment kernel leaves no light row to the whole
+    // wavefront: nor here, for its bits
+    const int64_t light_row = chunk < kMixedChunk ? chunk : light_row_slots(a.E, a.N, chunk);
+    p.walk = {a.rowptr, a.N, a.E, chunk, light_row, (a.E + chunk - 1) / chunk, w.head_row};
     int64_t per = ((a.N + 1023) / 1024 + kWave - 1) / kWave * kWave;
     p.zero_rows = per > kWave ? per : kWave;
     p.zero_items = (a.N + p.zero_rows - 1) / p.zero_rows;

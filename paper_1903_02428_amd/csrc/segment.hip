@@ -559,7 +559,7 @@ __device__ __forceinline__ void zero_empty_rows(const SegParams &p, int64_t z, i
 // sums lose nothing either (2M uniform edges 126 short, 120 mixed), max loses
 // its three more registers' worth of wavefronts (211 short, 220 mixed).
 constexpr int kHeavy = 0, kLightShort = 1, kLightMixed = 2;
-inline bool mixed_rows(const SegParams &p) { return p.chunk >= 64; }
+inline bool mixed_rows(const SegParams &p) { return p.chunk >= kMixedChunk; }
 
 // The lane number, unknown to the compiler to be the one before: what depends on
 // it is formed again instead of being kept in registers across the other kind of rows.

@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 F32, BF16 = torch.float32, torch.bfloat16
 # (N, E, F in 16-byte vectors, hub)
 CASES = [(1, 1, 1, False), (50, 333, 1, False), (300, 9000, 2, True), (140, 140 * 139 // 2, 5, False), (4000, 30000, 16, True),
-         (257, 6000, 25, False), (90, 5000, 64, True), (20000, 9000, 33, False)]
+         (257, 6000, 25, False), (90, 5000, 64, True), (20000, 9000, 33, False),
+         (20000, 200000, 2, False)]  # chunks of 32 slots, rows of up to 27
 
 
 @pytest.fixture(scope="module")
