@@ -309,6 +309,73 @@ def test_c5_attention_backward_sampled(pyg, c5, dev_graph):
     torch.cuda.empty_cache()
 
 
+def test_c5_gat_one_pass_sampled(pyg, c5):
+    """The one-pass attention and its gradients (8 heads of 16, fp32) where
+    rows of 512 bytes take the hub hint (column bit 31, non-temporal rows) and
+    the folds look at several chunks per wavefront: sampled targets (out, grad
+    a_dst) and sources (grad x, grad a_src), hubs among them, against 64-bit
+    torch sums over their whole neighbourhoods."""
+    N, H, C, slope = c5["N"], 8, 16, 0.2
+    rng = np.random.default_rng(83)
+    x = to_dev(c5["x"])
+    assert x.shape == (N, H * C)
+    g = to_dev(rng.standard_normal((N, H * C)).astype(np.float32))
+    a_src, a_dst = (to_dev(rng.standard_normal((N, H)).astype(np.float32)) for _ in range(2))
+    graph = pyg.Graph(to_dev(c5["edge_index_gcn"]), N)
+    dev = [t.clone().requires_grad_(True) for t in (x, a_src, a_dst)]
+    out = pyg.GATAttention.apply(*dev, graph, slope)
+    assert graph._map_t is None  # the one-pass kernels
+    gx, gs, gd = torch.autograd.grad(out, dev, g)
+    del graph, dev
+    ei = to_dev(c5["edge_index_gcn"])
+    as64, ad64 = a_src.double(), a_dst.double()
+
+    def alpha(src, dst):
+        v = as64[src] + ad64[dst]
+        return (v * torch.where(v >= 0, 1.0, slope)).exp() / Z[dst], torch.where(v >= 0, 1.0, slope)
+
+    def dots(src, dst):
+        p = g[dst].double().view(-1, H, C) * x[src].double().view(-1, H, C)
+        return p.sum(2), p.abs().sum(2)
+    # per target: Z, t = sum alpha <g, x> and the magnitudes of t
+    Z, t, st = (torch.zeros(N, H, dtype=torch.float64, device="cuda") for _ in range(3))
+    parts = ei.split(2_000_000, dim=1)
+    for src, dst in parts:
+        v = as64[src] + ad64[dst]
+        Z.index_add_(0, dst, (v * torch.where(v >= 0, 1.0, slope)).exp())
+    for src, dst in parts:
+        al, (ga, sa) = alpha(src, dst)[0], dots(src, dst)
+        t.index_add_(0, dst, al * ga), st.index_add_(0, dst, al * sa)
+    print("[c5] one-pass attention reference ok", flush=True)
+    rows = sample_rows(c5, n=250)[0]
+    nodes = to_dev(rows)
+    pick = torch.zeros(N, dtype=torch.bool, device="cuda")
+    pick[nodes] = True
+    # exp by the hardware exp2 of rounded scores, beside 1e-5 of every fp32 sum
+    top = float(max(a_src.abs().max(), a_dst.abs().max()))
+    rel = 2e-5 + 8 * 2.0 ** -24 * (1 + 2 * top)
+
+    def sums(at, val):
+        o = torch.zeros((N,) + val.shape[1:], dtype=torch.float64, device="cuda")
+        return o.index_add_(0, at, val)[nodes]
+    for side, (name_x, got_x), (name_a, got_a) in ((1, ("out", out), ("grad_dst", gd)),
+                                                   (0, ("grad_x", gx), ("grad_src", gs))):
+        src, dst = ei[:, pick[ei[side]]]
+        at = (src, dst)[side]
+        al, d = alpha(src, dst)
+        rows_of = (x[src] if side else g[dst]).double().view(-1, H, C)
+        ga, sa = dots(src, dst)
+        for name, got, val, mag in (
+                (name_x, got_x, al[..., None] * rows_of, al[..., None] * rows_of.abs()),
+                (name_a, got_a, al * (ga - t[dst]) * d, al * (sa + st[dst]))):
+            ref, m = (sums(at, v.reshape(v.shape[0], -1)) for v in (val, mag))
+            err = (got.detach()[nodes].double() - ref).abs()
+            assert bool((err <= rel * m + 1e-6).all()), (name, float((err - rel * m).max()))
+    print("[c5] one-pass attention ok", flush=True)
+    del parts
+    torch.cuda.empty_cache()
+
+
 def test_c5_edge_features_sampled(pyg, c5, dev_graph):
     """Edge-feature messages at the benchmark's shape: every edge of the large
     graph carries a 128-dimensional feature (counter-based, regenerable for
