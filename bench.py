@@ -43,16 +43,16 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, published peak
 # two source blocks, no per-edge norms, on the large power-law graph) from
 # rocprofv3 --pmc runs of this script (FETCH_SIZE, then WRITE_SIZE, then
 # TCC_HIT_sum + TCC_MISS_sum; KiB / counts per call, summed over the call's
-# five launches: d^-1/2, the row pre-scaling, the four windows, the long-row
-# fix-up and the block fold; the first three calls of each run, the timed
+# four launches: d^-1/2, the row pre-scaling, the four windows and the block
+# fold; the first three calls of each run, the timed
 # steps, before the detail calls), with FETCH_SIZE and WRITE_SIZE on a plain
 # 1024 MiB device copy for scale; see profiles/propagate_c5_counters.md.
 # They describe the sources with the recorded hash only: after any change to
 # those sources the traffic field is reported as null.
 COUNTERS = {
-    "source_hash": "a2d2b7630495b08d",
-    "fetch_kib": 12901985.6, "write_kib": 502042.8, "tcc_hit": 300259659.0, "tcc_miss": 210657761.3,
-    "copy_mib": 1024, "copy_fetch_kib": 524320.3, "copy_write_kib": 1048576.0,
+    "source_hash": "ae3cb32ad1f89ce6",
+    "fetch_kib": 12901639.6, "write_kib": 502022.8, "tcc_hit": 300481598.0, "tcc_miss": 210613319.0,
+    "copy_mib": 1024, "copy_fetch_kib": 524316.1, "copy_write_kib": 1048576.0,
 }
 # everything that decides which kernels a propagate call launches and how
 KERNEL_SOURCES = ["paper_1903_02428_amd/csrc/segment.hip", "paper_1903_02428_amd/csrc/common.hpp",
